@@ -10,10 +10,7 @@
 // keys k_{r,i} = sm64(sm64(seed, GROUP), 4r + i), restricted to [0, N) by
 // cycle walking (Black and Rogaway 2002).
 //
-// Reverse index: for each table t the pairs (bucket_t(x), cell of x in rep
-// r) over all points and repetitions are radix-sorted, duplicates dropped (a
-// filter bit is set once), and each bucket's offset is written by the one
-// sorted position where the bucket starts (no atomics, no count array).
+// The reverse index is built in lists.hip.
 //
 // Points arriving after the build (ids N0, N0+1, ...): the arrivals are cut
 // into blocks of B; within block j the point at position u joins group
@@ -21,10 +18,10 @@
 // on [0, 2^nb) (nb the smallest even width >= 2 covering B) restricted to
 // [0, B) by cycle walking, round keys sm64(sm64(seed, STREAM), 4(16j + r) + i).
 // Every complete block adds one point to each group, so group sizes stay
-// within two of each other.  An insert rebuilds each table's list from its
-// old entries plus the new pairs, and appends the new members (ascending id
-// is preserved: new ids exceed every old one) into copies of the member
-// arrays, growing their per-cell stride when a cell outgrows it.
+// within two of each other.  An insert merges the new points' cells into the
+// lists, and appends the new members (ascending id is preserved: new ids
+// exceed every old one) into copies of the member arrays, growing their
+// per-cell stride when a cell outgrows it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -65,27 +62,24 @@ __global__ void groups_kernel(uint64_t N, uint32_t R, uint32_t Rp, uint32_t B, u
     for (uint32_t r = R; r < Rp; ++r) grp[x * Rp + r] = grp[x * Rp + R - 1];
 }
 
-// keys[i] = group of point x0 + i in repetition r (rows from x0 on), vals[i] = its id
-__global__ void member_keys_kernel(const uint16_t *__restrict__ grp, uint64_t x0, uint64_t N,
-                                   uint32_t Rp, uint32_t r, uint64_t *__restrict__ keys,
-                                   uint32_t *__restrict__ vals) {
+// keys[q*n + i] = group of point x0 + i in repetition r0 + q
+__global__ void member_keys_kernel(const uint16_t *__restrict__ grp, uint64_t x0, uint64_t n,
+                                   uint32_t Rp, uint32_t r0, uint32_t *__restrict__ keys) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    keys[i] = grp[(x0 + i) * Rp + r];
-    vals[i] = (uint32_t)(x0 + i);
+    if (i >= n) return;
+    keys[(uint64_t)blockIdx.y * n + i] = grp[(x0 + i) * Rp + r0 + blockIdx.y];
 }
 
-// sorted position p of group b = keys[p] sits at run offset
-// p - (b*floor(N/B) + min(b, N mod B)); copy it to slot b*mstride + that.
-__global__ void member_slots_kernel(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ ids,
-                                    uint64_t N, uint32_t B, uint32_t mstride,
-                                    uint32_t *__restrict__ mem) {
+// sorted position p of group b = pairs[p] >> 32 sits at run offset
+// p - (b*floor(N/B) + min(b, N mod B)); its id goes to slot b*mstride + that.
+__global__ void member_slots_kernel(const uint64_t *__restrict__ pairs, uint64_t N, uint32_t B,
+                                    uint32_t mstride, uint32_t *__restrict__ mem) {
     const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
-    const uint64_t b = keys[p];
+    const uint64_t b = pairs[p] >> 32;
     const uint64_t q0 = N / B, rem = N % B;
     const uint64_t run = b * q0 + (b < rem ? b : rem);
-    mem[b * mstride + (p - run)] = ids[p];
+    mem[b * mstride + (p - run)] = (uint32_t)pairs[p];
 }
 
 // cmg[slot][r] = group in repetition r of the member stored in mem[slot]
@@ -140,18 +134,17 @@ void build_groups(Index &ix, hipStream_t s) {
     // members of each cell, ascending id: stable sort of ids by group, then
     // each group's run (at b*floor(N/B) + min(b, N mod B)) moves to its
     // 16-byte aligned slot b*mstride; unused slot tails hold 0xFFFFFFFF
-    DevBuf k1(N * 8, s), k2(N * 8, s), v1(N * 4, s), v2(N * 4, s);
+    DevBuf keys(N * 4, s), pairs(N * 8, s), tmp(N * 8, s), ps(pair_sort_scratch_bytes(N, 1), s);
     int gbits = 1;
     while ((1u << gbits) < B) ++gbits;
     FL_HIP(hipMemsetAsync(ix.mem, 0xFF, (size_t)R * B * ix.mstride * 4, s));
     for (uint32_t r = 0; r < R; ++r) {
         hipLaunchKernelGGL(member_keys_kernel, dim3(grid), dim3(256), 0, s, ix.grp, (uint64_t)0, N,
-                           ix.Rp, r, k1.as<uint64_t>(), v1.as<uint32_t>());
+                           ix.Rp, r, keys.as<uint32_t>());
         FL_CHECK_LAUNCH();
-        radix_sort_u64(k1.as<uint64_t>(), k2.as<uint64_t>(), v1.as<uint32_t>(), v2.as<uint32_t>(),
-                       N, gbits, s);
-        hipLaunchKernelGGL(member_slots_kernel, dim3(grid), dim3(256), 0, s, k1.as<uint64_t>(),
-                           v1.as<uint32_t>(), N, B, ix.mstride, ix.mem + (uint64_t)r * B * ix.mstride);
+        pair_sort(keys.as<uint32_t>(), N, 1, gbits, pairs.as<uint64_t>(), tmp.as<uint64_t>(), ps.ptr, s);
+        hipLaunchKernelGGL(member_slots_kernel, dim3(grid), dim3(256), 0, s, pairs.as<uint64_t>(), N, B,
+                           ix.mstride, ix.mem + (uint64_t)r * B * ix.mstride);
         FL_CHECK_LAUNCH();
     }
     const uint64_t nslots = (uint64_t)R * B * ix.mstride;
@@ -169,291 +162,11 @@ void build_groups(Index &ix, hipStream_t s) {
     FL_HIP(hipStreamSynchronize(s));  // the host vector is the copy's source
 }
 
-// ---------------------------------------------------------------------------
-// keys[x*R + r] = bucket_t(x) << cb | (r*Bp + g_r(x)) for the n points whose
-// codes and group rows are given
-__global__ void emit_pairs_kernel(const uint32_t *__restrict__ codes, const uint16_t *__restrict__ grp,
-                                  uint64_t N, uint32_t L, uint32_t t, uint32_t R, uint32_t Rp,
-                                  uint32_t Bp, int cb, uint64_t *__restrict__ keys) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N * R) return;
-    const uint64_t x = i / R;
-    const uint32_t r = (uint32_t)(i % R);
-    const uint64_t h = codes[x * L + t];
-    keys[i] = (h << cb) | (uint64_t)(r * Bp + grp[x * Rp + r]);
-}
-
-// The n entries of one table's existing list (positions e0 .. e0+n-1 of the
-// cells array) as sorted keys again: the bucket of an entry is the last one
-// whose offset does not exceed its position.
-template <typename CellT>
-__global__ void expand_list_kernel(const uint32_t *__restrict__ off, uint64_t nbk,
-                                   const CellT *__restrict__ cells, uint64_t e0, uint64_t n, int cb,
-                                   uint64_t *__restrict__ keys) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t pos = e0 + i;
-    uint64_t lo = 0, hi = nbk;  // off[lo] <= pos < off[hi]
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (off[mid] <= pos) lo = mid; else hi = mid;
-    }
-    keys[i] = (lo << cb) | (uint64_t)cells[pos];
-}
-
-// flag[i] = 1 for the first of each run of equal sorted keys
-__global__ void unique_kernel(const uint64_t *__restrict__ keys, uint64_t n,
-                              uint32_t *__restrict__ flag) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    flag[i] = (i == 0 || keys[i - 1] != keys[i]) ? 1u : 0u;
-}
-
-template <typename CellT>
-__global__ void compact_kernel(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ flag,
-                               const uint32_t *__restrict__ pos, uint64_t n, uint64_t cmask,
-                               const uint64_t *__restrict__ tbase, CellT *__restrict__ out) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || !flag[i]) return;
-    out[*tbase + pos[i]] = (CellT)(keys[i] & cmask);
-}
-
-// The running start of the tables' lists on the device: tb[t + 1] = tb[t] +
-// the unique entries of table t (pos and flag of its last key), so that the
-// tables' kernels queue without a host round trip per table.
-__global__ void list_total_kernel(const uint32_t *__restrict__ pos,
-                                  const uint32_t *__restrict__ flag, uint64_t n,
-                                  uint64_t *__restrict__ tb, uint32_t t) {
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        tb[t + 1] = tb[t] + (n ? (uint64_t)pos[n - 1] + flag[n - 1] : 0ull);
-}
-
-// Bucket offsets without atomics, as a merge of two sorted sequences: the
-// bucket numbers 0 .. nbk and the buckets of the n sorted keys, where bucket b
-// goes before the keys of buckets >= b.  The offset of bucket b is base plus
-// the unique entries among the keys before it.  Each thread takes OB_ITEMS
-// consecutive items of the merged order: a binary search on its diagonal finds
-// how many keys precede its first item, then it walks its items, consuming a
-// key or writing one offset per step.  The work per thread is bounded however
-// the keys crowd into few buckets (SRP codes of clustered data leave gaps of
-// millions of empty buckets); each offset is written exactly once.  32 items
-// per thread: a few thousand workgroups for a table of millions of keys.  A
-// workgroup's offsets form one contiguous run of at most OB_BLOCK buckets, so
-// they are gathered in LDS and written out with whole-line stores.
-constexpr uint32_t OB_ITEMS = 32;
-constexpr uint64_t OB_BLOCK = 256ull * OB_ITEMS;  // merged items per workgroup
-constexpr uint32_t OB_LDS = OB_BLOCK + OB_BLOCK / 32;  // one pad word per 32
-__device__ inline uint32_t ob_pad(uint64_t j) { return (uint32_t)(j + (j >> 5)); }
-
-// Where the merge path crosses diagonal d: the first key index i in [lo, hi)
-// that does not go before bucket d-1-i.
-__device__ inline uint64_t ob_cross(const uint64_t *__restrict__ keys, int cb, uint64_t d,
-                                    uint64_t lo, uint64_t hi) {
-    while (lo < hi) {
-        const uint64_t m = (lo + hi) / 2;
-        if ((keys[m] >> cb) + 1 + m < d) lo = m + 1;  // bucket(keys[m]) < d-1-m
-        else hi = m;
-    }
-    return lo;
-}
-
-// The crossings of the workgroups' first diagonals (one thread each): the
-// crossing only grows along the path, so a thread of bucket_offsets_kernel
-// then searches its workgroup's stretch of at most OB_BLOCK keys, mostly in
-// cache, instead of the whole table.
-__global__ void bucket_blocks_kernel(const uint64_t *__restrict__ keys, uint64_t n, int cb,
-                                     uint64_t nbk, uint64_t nblk, uint64_t *__restrict__ blo) {
-    const uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b > nblk) return;
-    const uint64_t total = nbk + 1 + n;
-    const uint64_t d = b * OB_BLOCK < total ? b * OB_BLOCK : total;
-    blo[b] = ob_cross(keys, cb, d, d > nbk + 1 ? d - (nbk + 1) : 0, d < n ? d : n);
-}
-
-__global__ __launch_bounds__(256) void bucket_offsets_kernel(const uint64_t *__restrict__ keys,
-                                                             const uint32_t *__restrict__ pos,
-                                                             const uint32_t *__restrict__ flag,
-                                                             uint64_t n, int cb, uint64_t nbk,
-                                                             const uint64_t *__restrict__ blo,
-                                                             const uint64_t *__restrict__ tbase,
-                                                             uint32_t *__restrict__ off) {
-    __shared__ uint32_t run[OB_LDS];
-    const uint64_t total = nbk + 1 + n;
-    const uint32_t base = (uint32_t)*tbase;  // an overflow past 2^32 fails the build
-    // the workgroup's diagonals [d0, d1) emit the buckets [b0, b1)
-    const uint64_t d0 = (uint64_t)blockIdx.x * OB_BLOCK;
-    const uint64_t d1 = d0 + OB_BLOCK < total ? d0 + OB_BLOCK : total;
-    const uint64_t c0 = blo[blockIdx.x], c1 = blo[blockIdx.x + 1];
-    const uint64_t b0 = d0 - c0, b1 = d1 - c1;
-    const uint64_t d = d0 + (uint64_t)threadIdx.x * OB_ITEMS;
-    if (d < total) {
-        // the crossing of d lies between those of the workgroup's diagonals
-        uint64_t lo = d > nbk + 1 ? d - (nbk + 1) : 0, hi = d < n ? d : n;
-        lo = lo > c0 ? lo : c0;
-        hi = hi < c1 ? hi : c1;
-        uint64_t i = ob_cross(keys, cb, d, lo, hi), b = d - i;
-        const uint32_t last = n ? pos[n - 1] + flag[n - 1] : 0u;
-        const uint64_t end = d + OB_ITEMS < total ? d + OB_ITEMS : total;
-        uint64_t kb = i < n ? keys[i] >> cb : 0;  // bucket of key i
-        uint32_t pv = 0;                          // pos of key i, once read
-        bool have = false;
-        for (uint64_t e = d; e < end; ++e) {
-            if (i < n && (b > nbk || kb < b)) {
-                ++i;
-                if (i < n) kb = keys[i] >> cb;
-                have = false;
-            } else {
-                if (!have) {
-                    pv = i < n ? pos[i] : last;
-                    have = true;
-                }
-                run[ob_pad(b - b0)] = base + pv;
-                ++b;
-            }
-        }
-    }
-    __syncthreads();
-    uint32_t *o = off + b0;
-    for (uint64_t j = threadIdx.x; j < b1 - b0; j += blockDim.x) o[j] = run[ob_pad(j)];
-}
-
-namespace {
-
-// The reverse index of all tables into fresh arrays: for table t the keys of
-// its old list (when `old_cells` is given: entries tstart_old[t] ..
-// tstart_old[t+1] of old_cells, offsets old_off) and the pairs of the n
-// points whose codes and group rows are given, sorted, deduplicated and
-// compacted.  Returns the new offsets [L][nbk+1] and cells (with the zeroed
-// 16-byte tail the query kernel's chunk reads need) and fills tstart.
-struct Lists {
-    uint32_t *offsets = nullptr;
-    void *cells = nullptr;
-    uint64_t entries = 0;
-    std::vector<uint64_t> tstart;
-};
-
-Lists assemble_lists(const Index &ix, const uint32_t *old_off, const void *old_cells,
-                     const std::vector<uint64_t> &tstart_old, const uint32_t *codes,
-                     const uint16_t *grp_rows, uint64_t n, hipStream_t s) {
-    const uint32_t L = ix.p.L, R = ix.p.R;
-    const uint32_t Bp = (ix.p.B + 3) & ~3u;
-    int cb = 1;
-    while ((1ull << cb) < (uint64_t)R * Bp) ++cb;
-    const uint64_t nbk = nbuckets(ix);
-    const int end_bit = (int)ix.nbits + cb;
-    const size_t csz = ix.cell_bytes;
-    const uint64_t nr = n * R;
-    uint64_t most_old = 0, old_total = 0;
-    if (old_cells)
-        for (uint32_t t = 0; t < L; ++t) {
-            most_old = std::max<uint64_t>(most_old, tstart_old[t + 1] - tstart_old[t]);
-            old_total += tstart_old[t + 1] - tstart_old[t];
-        }
-    const uint64_t most = most_old + nr;           // keys of the largest table
-    const uint64_t cap = old_total + nr * L;       // upper bound on the entries
-
-    Lists out;
-    out.tstart.assign(L + 1, 0);
-    DevBuf keys(most * 8, s), tmp(most * 8, s), flag(most * 4, s), pos(most * 4, s);
-    DevBuf tbd((L + 1) * 8, s);  // the tables' list starts
-    uint64_t *tb = tbd.as<uint64_t>();
-    const uint64_t nblk_most = (nbk + 1 + most + OB_BLOCK - 1) / OB_BLOCK;
-    DevBuf blod((nblk_most + 1) * 8, s);  // merge-path crossings per workgroup
-    void *big = nullptr;
-    try {
-        FL_HIP(hipMalloc(&out.offsets, (size_t)L * (nbk + 1) * 4));
-        FL_HIP(hipMalloc(&big, std::max<uint64_t>(cap, 1) * csz));
-        FL_HIP(hipMemsetAsync(tb, 0, 8, s));
-        for (uint32_t t = 0; t < L; ++t) {
-            const uint64_t nold = old_cells ? tstart_old[t + 1] - tstart_old[t] : 0;
-            const uint64_t nk = nold + nr;
-            uint64_t *k = keys.as<uint64_t>();
-            if (nold) {
-                const uint32_t *ot = old_off + (uint64_t)t * (nbk + 1);
-                const unsigned g = (unsigned)((nold + 255) / 256);
-                if (csz == 2)
-                    hipLaunchKernelGGL(expand_list_kernel<uint16_t>, dim3(g), dim3(256), 0, s, ot,
-                                       nbk, static_cast<const uint16_t *>(old_cells),
-                                       tstart_old[t], nold, cb, k);
-                else
-                    hipLaunchKernelGGL(expand_list_kernel<uint32_t>, dim3(g), dim3(256), 0, s, ot,
-                                       nbk, static_cast<const uint32_t *>(old_cells),
-                                       tstart_old[t], nold, cb, k);
-                FL_CHECK_LAUNCH();
-            }
-            if (nr) {
-                hipLaunchKernelGGL(emit_pairs_kernel, dim3((unsigned)((nr + 255) / 256)), dim3(256),
-                                   0, s, codes, grp_rows, n, L, t, R, ix.Rp, Bp, cb, k + nold);
-                FL_CHECK_LAUNCH();
-            }
-            // the sorted keys stay in whichever buffer the last pass wrote
-            uint64_t *ks = k;
-            radix_sort_u64(k, tmp.as<uint64_t>(), nullptr, nullptr, nk, end_bit, s, &ks);
-            if (nk) {
-                const unsigned g1 = (unsigned)((nk + 255) / 256);
-                hipLaunchKernelGGL(unique_kernel, dim3(g1), dim3(256), 0, s, ks, nk,
-                                   flag.as<uint32_t>());
-                FL_CHECK_LAUNCH();
-                device_exclusive_scan_u32(flag.as<uint32_t>(), pos.as<uint32_t>(), nk, s);
-                const uint64_t cmask = (1ull << cb) - 1;
-                // the list starts at tb[t]; big holds every key, so the
-                // writes stay inside it whatever the total comes to
-                if (csz == 2)
-                    hipLaunchKernelGGL(compact_kernel<uint16_t>, dim3(g1), dim3(256), 0, s, ks,
-                                       flag.as<uint32_t>(), pos.as<uint32_t>(), nk, cmask, tb + t,
-                                       static_cast<uint16_t *>(big));
-                else
-                    hipLaunchKernelGGL(compact_kernel<uint32_t>, dim3(g1), dim3(256), 0, s, ks,
-                                       flag.as<uint32_t>(), pos.as<uint32_t>(), nk, cmask, tb + t,
-                                       static_cast<uint32_t *>(big));
-                FL_CHECK_LAUNCH();
-            }
-            hipLaunchKernelGGL(list_total_kernel, dim3(1), dim3(64), 0, s, pos.as<uint32_t>(),
-                               flag.as<uint32_t>(), nk, tb, t);
-            FL_CHECK_LAUNCH();
-            const uint64_t nblk = (nbk + 1 + nk + OB_BLOCK - 1) / OB_BLOCK;
-            hipLaunchKernelGGL(bucket_blocks_kernel, dim3((unsigned)((nblk + 1 + 255) / 256)),
-                               dim3(256), 0, s, ks, nk, cb, nbk, nblk, blod.as<uint64_t>());
-            FL_CHECK_LAUNCH();
-            hipLaunchKernelGGL(bucket_offsets_kernel, dim3((unsigned)nblk), dim3(256), 0, s, ks,
-                               pos.as<uint32_t>(), flag.as<uint32_t>(), nk, cb, nbk,
-                               blod.as<uint64_t>(), tb + t, out.offsets + (uint64_t)t * (nbk + 1));
-            FL_CHECK_LAUNCH();
-        }
-        // one read-back of the tables' list starts
-        FL_HIP(hipMemcpyAsync(out.tstart.data(), tb, (L + 1) * 8, hipMemcpyDeviceToHost, s));
-        FL_HIP(hipStreamSynchronize(s));
-        const uint64_t base = out.tstart[L];
-        if (base > 0xFFFFFFFFull) fail(FLINNG_EINVAL, "reverse index exceeds 2^32 entries");
-        // shrink the list buffer to its size plus a zeroed tail, so that the
-        // query kernel's 16-byte chunk reads past a list's end stay inside it
-        const size_t used = (size_t)base * csz;
-        FL_HIP(hipMalloc(&out.cells, cells_alloc_bytes(base, csz)));
-        if (base) FL_HIP(hipMemcpyAsync(out.cells, big, used, hipMemcpyDeviceToDevice, s));
-        FL_HIP(hipMemsetAsync(static_cast<char *>(out.cells) + used, 0,
-                              cells_alloc_bytes(base, csz) - used, s));
-        FL_HIP(hipStreamSynchronize(s));
-        FL_HIP(hipFree(big));
-        big = nullptr;
-        out.entries = base;
-    } catch (...) {
-        if (big) (void)hipFree(big);
-        if (out.offsets) (void)hipFree(out.offsets);
-        if (out.cells) (void)hipFree(out.cells);
-        throw;
-    }
-    return out;
-}
-
-}  // namespace
-
 void build_lists(Index &ix, const uint32_t *codes, hipStream_t s) {
-    Lists l = assemble_lists(ix, nullptr, nullptr, {}, codes, ix.grp, ix.N, s);
-    if (ix.offsets) (void)hipFree(ix.offsets);
+    Lists l = make_lists(ix, codes, ix.grp, ix.N, s);
     ix.offsets = l.offsets;
     ix.cells = l.cells;
     ix.list_entries = l.entries;
-    ix.tstart = std::move(l.tstart);
 }
 
 // ---------------------------------------------------------------------------
@@ -478,14 +191,16 @@ __global__ void stream_groups_kernel(uint64_t x0, uint64_t n, uint64_t N0, uint3
     for (uint32_t r = R; r < Rp; ++r) grp[x * Rp + r] = grp[x * Rp + R - 1];
 }
 
-// Where each group's run starts and ends in the arrivals sorted by group.
-__global__ void run_bounds_kernel(const uint64_t *__restrict__ keys, uint64_t n,
+// Where each group's run starts and ends in the arrivals sorted by group (one
+// repetition per blockIdx.y).
+__global__ void run_bounds_kernel(const uint64_t *__restrict__ pairs, uint64_t n, uint32_t B,
                                   uint32_t *__restrict__ start, uint32_t *__restrict__ end) {
     const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
-    const uint64_t b = keys[p];
-    if (p == 0 || keys[p - 1] != b) start[b] = (uint32_t)p;
-    if (p == n - 1 || keys[p + 1] != b) end[b] = (uint32_t)(p + 1);
+    const uint64_t *v = pairs + (uint64_t)blockIdx.y * n;
+    const uint64_t b = v[p] >> 32, o = (uint64_t)blockIdx.y * B + b;
+    if (p == 0 || v[p - 1] >> 32 != b) start[o] = (uint32_t)p;
+    if (p == n - 1 || v[p + 1] >> 32 != b) end[o] = (uint32_t)(p + 1);
 }
 
 __global__ void run_counts_kernel(const uint32_t *__restrict__ start, const uint32_t *__restrict__ end,
@@ -505,20 +220,21 @@ __global__ void restride_kernel(const uint32_t *__restrict__ mem, const uint16_t
     for (uint32_t r = 0; r < Rp; ++r) cmg1[(c * s1 + j) * Rp + r] = cmg[i * Rp + r];
 }
 
-// The sorted arrivals of one repetition join their cells after the members
-// already there: member id and its group row.
-__global__ void place_members_kernel(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ ids,
-                                     uint64_t n, const uint32_t *__restrict__ start,
-                                     const uint32_t *__restrict__ gsize_r, uint32_t mstride,
+// The sorted arrivals of a repetition (blockIdx.y) join their cells after the
+// members already there: member id x0 + index and its group row.
+__global__ void place_members_kernel(const uint64_t *__restrict__ pairs, uint64_t n, uint64_t x0,
+                                     const uint32_t *__restrict__ start,
+                                     const uint32_t *__restrict__ gsize, uint32_t B, uint32_t mstride,
                                      const uint16_t *__restrict__ grp, uint32_t Rp,
-                                     uint32_t *__restrict__ mem_r, uint16_t *__restrict__ cmg_r) {
+                                     uint32_t *__restrict__ mem, uint16_t *__restrict__ cmg) {
     const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
-    const uint64_t b = keys[p];
-    const uint64_t slot = b * mstride + gsize_r[b] + (p - start[b]);
-    const uint32_t x = ids[p];
-    mem_r[slot] = x;
-    for (uint32_t r = 0; r < Rp; ++r) cmg_r[slot * Rp + r] = grp[(uint64_t)x * Rp + r];
+    const uint64_t v = pairs[(uint64_t)blockIdx.y * n + p];
+    const uint64_t c = (uint64_t)blockIdx.y * B + (v >> 32);  // cell (r, b)
+    const uint64_t slot = c * mstride + gsize[c] + (p - start[c]);
+    const uint64_t x = x0 + (uint32_t)v;
+    mem[slot] = (uint32_t)x;
+    for (uint32_t r = 0; r < Rp; ++r) cmg[slot * Rp + r] = grp[x * Rp + r];
 }
 
 __global__ void add_u32_kernel(const uint32_t *__restrict__ a, const uint32_t *__restrict__ b,
@@ -557,24 +273,18 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         // 2. arrivals sorted by group, per repetition; new cell sizes
         int gbits = 1;
         while ((1u << gbits) < B) ++gbits;
-        std::vector<DevBuf> skeys, sids;
-        DevBuf tk(n * 8, s), tv(n * 4, s), starts(ncells * 4, s), ends(ncells * 4, s),
-            cnt(ncells * 4, s);
+        DevBuf skeys(n * R * 4, s), pairs(n * R * 8, s), tmp(n * R * 8, s),
+            ps(pair_sort_scratch_bytes(n, R), s);
+        DevBuf starts(ncells * 4, s), ends(ncells * 4, s), cnt(ncells * 4, s);
         FL_HIP(hipMemsetAsync(starts.ptr, 0, ncells * 4, s));
         FL_HIP(hipMemsetAsync(ends.ptr, 0, ncells * 4, s));
-        for (uint32_t r = 0; r < R; ++r) {
-            skeys.emplace_back(n * 8, s);
-            sids.emplace_back(n * 4, s);
-            hipLaunchKernelGGL(member_keys_kernel, dim3(gn), dim3(256), 0, s, grp, x0, n, Rp, r,
-                               skeys.back().as<uint64_t>(), sids.back().as<uint32_t>());
-            FL_CHECK_LAUNCH();
-            radix_sort_u64(skeys.back().as<uint64_t>(), tk.as<uint64_t>(), sids.back().as<uint32_t>(),
-                           tv.as<uint32_t>(), n, gbits, s);
-            hipLaunchKernelGGL(run_bounds_kernel, dim3(gn), dim3(256), 0, s,
-                               skeys.back().as<uint64_t>(), n, starts.as<uint32_t>() + (uint64_t)r * B,
-                               ends.as<uint32_t>() + (uint64_t)r * B);
-            FL_CHECK_LAUNCH();
-        }
+        hipLaunchKernelGGL(member_keys_kernel, dim3(gn, R), dim3(256), 0, s, grp, x0, n, Rp, 0u,
+                           skeys.as<uint32_t>());
+        FL_CHECK_LAUNCH();
+        pair_sort(skeys.as<uint32_t>(), n, R, gbits, pairs.as<uint64_t>(), tmp.as<uint64_t>(), ps.ptr, s);
+        hipLaunchKernelGGL(run_bounds_kernel, dim3(gn, R), dim3(256), 0, s, pairs.as<uint64_t>(), n, B,
+                           starts.as<uint32_t>(), ends.as<uint32_t>());
+        FL_CHECK_LAUNCH();
         hipLaunchKernelGGL(run_counts_kernel, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0, s,
                            starts.as<uint32_t>(), ends.as<uint32_t>(), (uint32_t)ncells,
                            cnt.as<uint32_t>());
@@ -605,22 +315,17 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
                                ix.mem, ix.cmg, ncells, ix.mstride, ms1, Rp, mem1, cmg1);
             FL_CHECK_LAUNCH();
         }
-        for (uint32_t r = 0; r < R; ++r) {
-            hipLaunchKernelGGL(place_members_kernel, dim3(gn), dim3(256), 0, s,
-                               skeys[r].as<uint64_t>(), sids[r].as<uint32_t>(), n,
-                               starts.as<uint32_t>() + (uint64_t)r * B, ix.gsize + (uint64_t)r * B,
-                               ms1, grp, Rp, mem1 + (uint64_t)r * B * ms1,
-                               cmg1 + (uint64_t)r * B * ms1 * Rp);
-            FL_CHECK_LAUNCH();
-        }
+        hipLaunchKernelGGL(place_members_kernel, dim3(gn, R), dim3(256), 0, s, pairs.as<uint64_t>(), n,
+                           x0, starts.as<uint32_t>(), ix.gsize, B, ms1, grp, Rp, mem1, cmg1);
+        FL_CHECK_LAUNCH();
         FL_HIP(hipMalloc(&cfl1, ncells * ms1 * 4));
         build_filter(ix, mem1, grp, ms1, cfl1, s);
         FL_HIP(hipMalloc(&gsize1, ncells * 4));
         hipLaunchKernelGGL(add_u32_kernel, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0, s,
                            ix.gsize, cnt.as<uint32_t>(), ncells, gsize1);
         FL_CHECK_LAUNCH();
-        // 4. reverse index: old entries plus the arrivals' pairs
-        lists = assemble_lists(ix, ix.offsets, ix.cells, ix.tstart, codes, grp + x0 * Rp, n, s);
+        // 4. reverse index: the arrivals' cells merged into the old lists
+        lists = merge_lists(ix, codes, grp + x0 * Rp, n, s);
         FL_HIP(hipStreamSynchronize(s));
         // 5. swap the new version in while no query is being enqueued, and
         //    free the old one once the device has finished all work using it
@@ -630,7 +335,6 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         ix.offsets = lists.offsets;
         ix.cells = lists.cells;
         ix.list_entries = lists.entries;
-        ix.tstart = std::move(lists.tstart);
         ix.mem = mem1;
         ix.cmg = cmg1;
         ix.cfl = cfl1;
@@ -658,8 +362,7 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         dfree(cmg1);
         dfree(cfl1);
         dfree(gsize1);
-        dfree(lists.offsets);
-        dfree(lists.cells);
+        free_lists(lists);
         throw;
     }
 }

@@ -104,7 +104,6 @@ struct Index {
     uint32_t *gsize = nullptr;
     uint32_t gmax = 0;                    // the largest cell
     std::vector<uint32_t> gsize_host;     // host copy of gsize
-    std::vector<uint64_t> tstart;         // [L+1] first list entry of each table
     mutable std::shared_mutex rw;         // query enqueue (shared) / insert swap
     std::mutex insert_mu;                 // one insert at a time
     // Device scratch for the codes of one query batch, one region per
@@ -244,16 +243,32 @@ struct CopySeg {
 constexpr int MAX_COPY_SEGS = 128;  // per launch (kernel-argument space)
 void copy_segments(const CopySeg *segs, size_t nseg, hipStream_t s);
 
-// Sorting and scans (radix.hip).
-void device_exclusive_scan_u32(const uint32_t *in, uint32_t *out, uint64_t n,
-                               hipStream_t s);
-// Stable LSD radix sort of 64-bit keys (bits [0, end_bit)) with optional
-// uint32 values; result in keys/vals (tmp buffers of the same size needed).
-// Keys alone (vals == nullptr) with `sorted` given: the result stays in
-// whichever of keys / keys_tmp the last pass wrote, returned in *sorted.
-void radix_sort_u64(uint64_t *keys, uint64_t *keys_tmp, uint32_t *vals,
-                    uint32_t *vals_tmp, uint64_t n, int end_bit, hipStream_t s,
-                    uint64_t **sorted = nullptr);
+// Sorting and scans (radix.hip).  Exclusive scan of data[0, n) in place, each
+// prefix plus base (32-bit, wrapping); *total (device) = base + the sum, 64-bit.
+size_t scan_scratch_bytes(uint64_t n);
+void device_exclusive_scan_u32(uint32_t *data, uint64_t n, uint64_t base, uint64_t *total,
+                               void *scratch, hipStream_t s);
+// `count` stable sorts of n keys below 2^bits (sort t: keys[t*n ..]) into
+// out[t*n ..] = key << 32 | index; tmp: as large as out.
+size_t pair_sort_scratch_bytes(uint64_t n, uint32_t count);
+void pair_sort(const uint32_t *keys, uint64_t n, uint32_t count, int bits, uint64_t *out,
+               uint64_t *tmp, void *scratch, hipStream_t s);
+
+// The reverse index (lists.hip): offsets [L][2^bits + 1] and cells (with the
+// zeroed 16-byte tail that the query kernel's chunk reads need), owned by the
+// caller.
+struct Lists {
+    uint32_t *offsets = nullptr;
+    void *cells = nullptr;
+    uint64_t entries = 0;
+};
+// Lists of n points with codes [n][L] and group rows [n][Rp].
+Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, uint64_t n,
+                 hipStream_t s);
+// The index's lists with the cells of n more points merged in, as new arrays.
+Lists merge_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp_rows, uint64_t n,
+                  hipStream_t s);
+void free_lists(Lists &l);
 
 // Build pieces (build.hip).
 void build_groups(Index &ix, hipStream_t s);
