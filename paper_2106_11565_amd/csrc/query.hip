@@ -697,17 +697,110 @@ __device__ inline void walk_flat_filtered(const uint32_t *lbs, const uint32_t *f
     }
 }
 
-// m and c* of one member from its group row (general-k path).
-__device__ inline void slot_min_cell(const uint16_t *row, uint32_t R, uint32_t Bp, const uint8_t *cnt8,
-                                     uint32_t &m, uint32_t &cs) {
-    m = 0xFFFFFFFFu;
-    cs = 0;
-    for (uint32_t r = 0; r < R; ++r) {
-        const uint32_t c = r * Bp + row[r];
-        const uint32_t v = 255u - cnt8[c];
-        if (v <= m) {
-            m = v;
-            cs = c;
+// General k: the members of the listed cells as one flattened sequence (lps:
+// the cells' exclusive size sums), V positions per thread and round, kept keys
+// below the threshold appended to the LDS buffer.  Where the pass filters, a
+// member's filter word is read first and its id and row only if it survives
+// (walk_cells_filtered).  A round adds at most T*V keys, so the workgroup only
+// meets to look at the buffer when it could overflow (`room` counts down), and
+// only sorts and cuts it to k, tightening the threshold, when it would.
+struct AppendState {
+    uint64_t thr;   // keys at or above it cannot be among the k smallest
+    uint32_t room;  // keys that surely still fit (uniform)
+    uint32_t n_ge, n_all, gathered;
+};
+
+template <int RP, int T>
+__device__ inline void walk_append(const uint32_t *lbs, const uint32_t *lps, uint32_t nl, uint32_t total,
+                                   const uint32_t *__restrict__ memr, const uint16_t *__restrict__ cmgr,
+                                   const uint32_t *__restrict__ cflr, uint32_t R, uint32_t Bp,
+                                   uint32_t mstride, uint32_t level, bool keep, bool filt, uint32_t f1b,
+                                   uint32_t f2b, uint32_t V, uint32_t k, uint32_t cap, uint64_t *buf,
+                                   uint32_t *misc, AppendState &as) {
+    constexpr int RW = (RP + 1) / 2;
+    const int tid = threadIdx.x, lane = tid % 64;
+    const uint32_t lim = 256u - level;
+    uint32_t rb[RP];
+#pragma unroll
+    for (int r = 0; r < RP; ++r) rb[r] = ((uint32_t)r < R ? (uint32_t)r : R - 1) * Bp;
+    for (uint32_t off = 0; off < total; off += T * V) {
+        if (as.room < T * V) {
+            __syncthreads();
+            const uint32_t nb = misc[M_BUFN];
+            __syncthreads();
+            if (nb > cap - T * V) {
+                for (uint32_t i = nb + tid; i < cap; i += T) buf[i] = ~0ull;
+                __syncthreads();
+                wg_bitonic<T>(buf, cap);
+                if (tid == 0) misc[M_BUFN] = nb < k ? nb : k;
+                if (nb >= k) as.thr = buf[k - 1];
+                as.room = cap - (nb < k ? nb : k);
+                __syncthreads();
+            } else {
+                as.room = cap - nb;
+            }
+        }
+        as.room -= T * V;
+        uint64_t slot[4];
+        uint32_t fw[4];
+        uint32_t pend = 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t idx = off + (uint32_t)g * T + tid;
+            const bool valid = (uint32_t)g < V && idx < total;
+            uint32_t lo = 0, hi = valid ? nl : 0;  // the last cell that starts at or before idx
+            while (hi > lo + 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (lps[mid] <= idx) lo = mid; else hi = mid;
+            }
+            slot[g] = valid ? (uint64_t)lbs[lo] * mstride + (idx - lps[lo]) : 0ull;
+            fw[g] = filt ? cflr[slot[g]] : 0u;
+            if (valid) pend |= 1u << g;
+        }
+        if (filt) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const uint32_t b1 = lds_u8_at(f1b + (fw[g] & 0xFFFFu));
+                const uint32_t b2 = lds_u8_at(f2b + (fw[g] >> 16));
+                if (b1 >= lim || b2 >= lim) pend &= ~(1u << g);
+            }
+        }
+        while (__ballot(pend != 0)) {
+            const bool act = pend != 0;
+            const uint32_t m = act ? (uint32_t)__builtin_ctz(pend) : 0u;
+            pend &= pend - 1;
+            uint64_t sl = slot[0];
+#pragma unroll
+            for (int g = 1; g < 4; ++g) sl = m == (uint32_t)g ? slot[g] : sl;
+            uint32_t xid = 0, rw[RW];
+#pragma unroll
+            for (int i = 0; i < RW; ++i) rw[i] = 0;
+            if (act) {
+                xid = memr[sl];
+                load_row1<RP>(cmgr + sl * RP, rw);
+            }
+            uint32_t t = 0;
+#pragma unroll
+            for (int r = 0; r < RP; ++r) {
+                const uint32_t c = rb[r] + ((rw[r >> 1] >> (16 * (r & 1))) & 0xFFFFu);
+                const uint32_t tv = (lds_u8_at(c) << 24) | c;
+                t = tv > t ? tv : t;
+            }
+            const unsigned long long am = __ballot(act);
+            const unsigned long long gm = __ballot(act && t < (lim << 24));
+            as.gathered += (uint32_t)__popcll(am);
+            as.n_ge += (uint32_t)__popcll(gm);
+            as.n_all += (uint32_t)__popcll(keep ? am : gm);
+            const uint64_t key = ((uint64_t)t << 32) | xid;
+            const unsigned long long tm = __ballot(key < as.thr) & (keep ? am : gm);
+            if (tm) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&misc[M_BUFN], (uint32_t)__popcll(tm));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                at += __builtin_amdgcn_mbcnt_hi((uint32_t)(tm >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)tm, 0u));
+                if (__builtin_amdgcn_inverse_ballot_w64(tm)) buf[at] = key;
+            }
         }
     }
 }
@@ -1204,93 +1297,76 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
             }
             if (QW * k > 64) __syncthreads();
           } else {
-            // General k: cells 256 at a time, candidates appended to a
-            // capacity-cap LDS buffer under a tightening threshold; the
-            // buffer is sorted and cut to k when nearly full.
-            uint32_t n_ge = 0, n_all = 0;  // per-wave tallies (lane 0 of each wave)
-            unsigned long long pass_members = 0;
-            for (uint32_t cb0 = 0; cb0 < B; cb0 += QT) {
-                const uint32_t b = cb0 + tid;
-                uint32_t cval = 0;
-                if (b < B) cval = 255u - cnt8[rep * Bp + b];
-                const bool pos = (b < B) && (cval >= level);
-                const uint32_t sz = pos ? A.gsize[rep * B + b] : 0u;
-                uint32_t npos, tsz;
-                const uint32_t ci = wg_excl_scan<QT>(pos ? 1u : 0u, scr, &npos);
-                const uint32_t ps = wg_excl_scan<QT>(sz, scr, &tsz);
-                if (pos) {
-                    lb[ci] = b;
-                    lp[ci] = ps;
-                }
-                pass_members += tsz;
+            // General k: the positive cells of `rep` in an LDS list (all of
+            // them, or QT at a time when they do not fit), their members
+            // walked and the kept keys collected in the LDS buffer, which is
+            // sorted once at the end.
+            AppendState as{~0ull, cap, 0u, 0u, 0u};
+            const bool filt = !keep && R >= 2;
+            const uint32_t *cflr = A.cfl + rep * rstride;
+            const uint32_t f1b = ((rep + 1) % R) * Bp, f2b = ((rep + 2) % R) * Bp;
+            const uint32_t V = (cap - k) / QT < 4 ? (cap - k) / QT : 4;
+            uint32_t pass_members = 0;
+            auto walk = [&](uint32_t nl) {  // nl <= QT listed cells
+                uint32_t tot;
+                const uint32_t sz = (uint32_t)tid < nl ? A.gsize[rep * B + lb[tid]] : 0u;
+                const uint32_t ex = wg_excl_scan<QT>(sz, scr, &tot);
+                if ((uint32_t)tid < nl) lp[tid] = ex;
                 __syncthreads();
-                for (uint32_t off = 0; off < tsz; off += QT) {
-                    const uint32_t idx = off + tid;
-                    bool take = false;
-                    uint64_t key = 0;
-                    bool ge = false;
-                    if (idx < tsz) {
-                        uint32_t lo = 0, hi = npos;
-                        while (hi - lo > 1) {
-                            uint32_t mid = (lo + hi) >> 1;
-                            if (lp[mid] <= idx) lo = mid; else hi = mid;
-                        }
-                        const uint64_t slot = (uint64_t)lb[lo] * A.mstride + (idx - lp[lo]);
-                        const uint32_t x = memr[slot];
-                        uint32_t m, cs;
-                        slot_min_cell(cmgr + slot * RP, R, Bp, cnt8, m, cs);
-                        ge = m >= level;
-                        take = keep || ge;
-                        key = ((uint64_t)(255u - m) << 56) | ((uint64_t)cs << 32) | x;
-                        if (take) {
-                            const uint64_t thr = ((uint64_t)misc[M_THRHI] << 32) | misc[M_THRLO];
-                            if (key < thr) {
-                                const uint32_t slotb = atomicAdd(&misc[M_BUFN], 1u);
-                                buf[slotb] = key;
-                            }
-                        }
+                pass_members += tot;
+                walk_append<RP, QT>(lb, lp, nl, tot, memr, cmgr, cflr, R, Bp, A.mstride, level, keep,
+                                    filt, f1b, f2b, V, k, cap, buf, misc, as);
+            };
+            const uint32_t nrep = hist[rep * (L + 1) + level];
+            if (nrep <= CL) {
+                for (uint32_t w = tid; w < Bp / 4; w += QT) {
+                    const uint32_t v = ~cnt32[rep * (Bp / 4) + w];  // four counts
+                    if (!v) continue;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t b = 4 * w + j;
+                        if (b < B && ((v >> (8 * j)) & 255u) >= level)
+                            lb[atomicAdd(&misc[M_LCNT], 1u)] = b;
                     }
-                    const unsigned long long mg = __ballot(take && ge);
-                    const unsigned long long ma = __ballot(take);
-                    if (lane == 0) {
-                        n_ge += __popcll(mg);
-                        n_all += __popcll(ma);
-                    }
+                }
+                __syncthreads();
+                walk(nrep);
+            } else {
+                for (uint32_t cb0 = 0; cb0 < B; cb0 += QT) {
+                    const uint32_t b = cb0 + tid;
+                    const bool pos = (b < B) && (255u - cnt8[rep * Bp + b] >= level);
+                    const unsigned long long pm = __ballot(pos);
+                    uint32_t wbase = 0;
+                    if (lane == 0 && pm) wbase = atomicAdd(&misc[M_LCNT], (uint32_t)__popcll(pm));
+                    wbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)wbase);
+                    if (pos)
+                        lb[wbase + __builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u))] = b;
                     __syncthreads();
-                    if (misc[M_BUFN] > cap - QT) {
-                        // merge: sort, keep the k smallest, tighten the threshold
-                        const uint32_t nb = misc[M_BUFN];
-                        for (uint32_t i = nb + tid; i < cap; i += QT) buf[i] = ~0ull;
+                    const uint32_t nl = misc[M_LCNT];
+                    if (nl > CL - QT || cb0 + QT >= B) {
+                        walk(nl);
                         __syncthreads();
-                        wg_bitonic<QT>(buf, cap);
-                        if (tid == 0) {
-                            const uint32_t keepn = nb < k ? nb : k;
-                            misc[M_BUFN] = keepn;
-                            if (keepn == k) {
-                                misc[M_THRLO] = (uint32_t)buf[k - 1];
-                                misc[M_THRHI] = (uint32_t)(buf[k - 1] >> 32);
-                            }
-                        }
+                        if (tid == 0) misc[M_LCNT] = 0;
                         __syncthreads();
                     }
                 }
-                __syncthreads();
             }
             if (lane == 0) {
-                atomicAdd(&misc[M_NGE], n_ge);
-                atomicAdd(&misc[M_NALL], n_all);
+                atomicAdd(&misc[M_NGE], as.n_ge);
+                atomicAdd(&misc[M_NALL], as.n_all);
+                atomicAdd(&misc[M_GATH], as.gathered);
             }
-            if (tid == 0) {
-                atomicAdd(&misc[M_MEMB], (uint32_t)pass_members);
-                atomicAdd(&misc[M_GATH], (uint32_t)pass_members);
-            }
+            if (tid == 0) atomicAdd(&misc[M_MEMB], pass_members);
             __syncthreads();
-            {
+            if (misc[M_NGE] >= k || keep) {  // only a final pass needs the order
                 const uint32_t nb = misc[M_BUFN];
-                for (uint32_t i = nb + tid; i < cap; i += QT) buf[i] = ~0ull;
+                uint32_t sz = 2;
+                while (sz < nb) sz <<= 1;  // at most cap, a power of two
+                for (uint32_t i = nb + tid; i < sz; i += QT) buf[i] = ~0ull;
+                __syncthreads();
+                wg_bitonic<QT>(buf, sz);
             }
-            __syncthreads();
-            wg_bitonic<QT>(buf, cap);
           }
             const uint32_t nge = misc[M_NGE], nall = misc[M_NALL];
             const bool ok = nge >= k;
@@ -1424,6 +1500,15 @@ static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool spar
     }
     while (sh.hc & (sh.hc - 1)) sh.hc &= sh.hc - 1;  // round down to a power of two
     sh.cap = cap_for(k, sh.T);
+    // general k: up to four appends per thread and round where the workgroup's
+    // share of the LDS has the room
+    if (gk) {
+        const size_t share = sh.T == 256 && small * 4 <= lim ? lim / 4 : lim;
+        while (sh.cap < k + 4u * (uint32_t)sh.T &&
+               q_layout(L, R, Bp, sh.cap * 2, sh.T, 1, gk).total <= share)
+            sh.cap *= 2;
+        while (sh.hc > 1 && q_layout(L, R, Bp, sh.cap, sh.T, sh.hc, gk).total > share) sh.hc >>= 1;
+    }
     sh.lds = q_layout(L, R, Bp, sh.cap, sh.T, sh.hc, gk).total;
     return sh;
 }
