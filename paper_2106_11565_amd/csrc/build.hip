@@ -167,6 +167,7 @@ void build_lists(Index &ix, const uint32_t *codes, hipStream_t s) {
     ix.offsets = l.offsets;
     ix.cells = l.cells;
     ix.list_entries = l.entries;
+    ix.mean_entries = l.mean_entries;
 }
 
 // ---------------------------------------------------------------------------
@@ -334,6 +335,8 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
                         grp1 ? ix.grp : nullptr};
         ix.offsets = lists.offsets;
         ix.cells = lists.cells;
+        // (kept as it was, scaled: it only chooses between query kernels)
+        ix.mean_entries *= (double)lists.entries / (double)std::max<uint64_t>(ix.list_entries, 1);
         ix.list_entries = lists.entries;
         ix.mem = mem1;
         ix.cmg = cmg1;

@@ -89,6 +89,7 @@ struct Index {
     uint32_t mstride = 4;        // member slots per cell
     uint32_t cell_bytes = 2;
     uint64_t list_entries = 0;
+    double mean_entries = 0;     // list entries one of the points meets as a query
     uint64_t device_bytes = 0;
     uint64_t srp_rechecked = 0, srp_exact = 0;
     int device = 0;
@@ -261,6 +262,7 @@ struct Lists {
     uint32_t *offsets = nullptr;
     void *cells = nullptr;
     uint64_t entries = 0;
+    double mean_entries = 0;  // entries that one of the points meets as a query
 };
 // Lists of n points with codes [n][L] and group rows [n][Rp].
 Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, uint64_t n,

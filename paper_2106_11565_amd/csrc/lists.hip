@@ -106,14 +106,15 @@ __device__ inline uint32_t row_half(const uint32_t (&w)[W], int r) {
 }
 
 // COUNT: cnt[i] = list length of the run that starts at sorted point i (0
-// where none starts, and for now where a long one does), and the long runs'
-// starts appended to `longs`.  Otherwise: the cells of the short runs, the
+// where none starts, and for now where a long one does), the long runs' starts
+// appended to `longs`, and list lengths times run lengths added to `work`.  Otherwise: the cells of the short runs, the
 // list of the run that starts at i beginning at cells[pos[i]].
 template <typename CellT, int RP, bool COUNT>
 __global__ __launch_bounds__(256) void short_runs_kernel(
     const uint64_t *__restrict__ pairs, uint64_t n, const uint16_t *__restrict__ grp, uint32_t R,
     uint32_t Bp, uint32_t *__restrict__ cnt, uint64_t *__restrict__ longs,
-    unsigned int *__restrict__ nlong, CellT *__restrict__ cells) {
+    unsigned int *__restrict__ nlong, unsigned long long *__restrict__ work,
+    CellT *__restrict__ cells) {
     constexpr int W = RowWords<RP>::W;
     constexpr int PER = (RUN_LOAD + 255) / 256;
     __shared__ uint32_t sc[RUN_LOAD + 1];  // sc[j + 1]: code of point base + j
@@ -189,6 +190,12 @@ __global__ __launch_bounds__(256) void short_runs_kernel(
             const uint32_t j = tid + 256 * p;
             if (base + j < n) cnt[o + base + j] = aux[j];
         }
+        uint32_t sum = 0;  // list entries met by the runs' points as queries
+#pragma unroll
+        for (int p = 0; p < PER; ++p) sum += act[p] ? aux[st[p]] : 0u;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if (tid % 64 == 0 && sum) atomicAdd(work, (unsigned long long)sum);
     } else {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
@@ -235,10 +242,12 @@ __global__ __launch_bounds__(256) void long_runs_kernel(const uint64_t *__restri
                                                         const uint64_t *__restrict__ longs,
                                                         const unsigned int *__restrict__ nlong,
                                                         uint32_t *__restrict__ cnt,
+                                                        unsigned long long *__restrict__ work,
                                                         CellT *__restrict__ cells) {
     constexpr int W = RowWords<RP>::W;
     extern __shared__ uint32_t bits[];
     __shared__ uint32_t wsum[4];
+    __shared__ uint32_t npts;
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
     const unsigned int total = *nlong;
     for (unsigned int q = blockIdx.x; q < total; q += gridDim.x) {
@@ -246,7 +255,9 @@ __global__ __launch_bounds__(256) void long_runs_kernel(const uint64_t *__restri
         const uint64_t end = f / n * n + n;  // of its table
         const uint32_t c = (uint32_t)(pairs[f] >> 32);
         for (uint32_t w = tid; w < nwords; w += 256) bits[w] = 0;
+        if (COUNT && tid == 0) npts = 0;
         __syncthreads();
+        uint32_t mine_pts = 0;
         for (uint64_t p = f + 64 * wave;; p += 256) {
             const uint64_t v = p + lane < end ? pairs[p + lane] : ~0ull;
             const bool in = (uint32_t)(v >> 32) == c;
@@ -261,8 +272,10 @@ __global__ __launch_bounds__(256) void long_runs_kernel(const uint64_t *__restri
                     }
                 }
             }
+            mine_pts += (uint32_t)__popcll(__ballot(in));
             if (__ballot(!in)) break;  // the run ends inside this piece
         }
+        if (COUNT && lane == 0) atomicAdd(&npts, mine_pts);
         __syncthreads();
         if constexpr (COUNT) {
             uint32_t s = 0;
@@ -271,7 +284,11 @@ __global__ __launch_bounds__(256) void long_runs_kernel(const uint64_t *__restri
             for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
             if (lane == 0) wsum[wave] = s;
             __syncthreads();
-            if (tid == 0) cnt[f] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+            if (tid == 0) {
+                const uint32_t len = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+                cnt[f] = len;
+                atomicAdd(work, (unsigned long long)len * npts);
+            }
         } else {
             uint32_t at = cnt[f];
             for (uint32_t w0 = 0; w0 < nwords; w0 += 256) {
@@ -301,12 +318,12 @@ __global__ __launch_bounds__(256) void long_runs_kernel(const uint64_t *__restri
     }
 }
 
-// tstart[t] = where table t's entries start: the prefix at its first point
-// (the total after the last table is written by the scan).
+// tstart[t] = where table t's entries start: the prefix at its first point,
+// and the total after the last table.
 __global__ void table_starts_kernel(const uint32_t *__restrict__ pos, uint64_t n, uint32_t nt,
-                                    uint64_t *__restrict__ tstart) {
+                                    const uint64_t *__restrict__ total, uint64_t *__restrict__ tstart) {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < nt) tstart[t] = pos[(uint64_t)t * n];
+    if (t <= nt) tstart[t] = t < nt ? pos[(uint64_t)t * n] : *total;
 }
 
 // ---------------------------------------------------------------------------
@@ -522,6 +539,7 @@ struct Batch {
     uint64_t *longs;
     unsigned int *nlong;
     uint64_t *tstart;  // [nt + 1]
+    uint64_t *total;   // entries so far, and the work of the runs
     uint64_t *blo;
 };
 
@@ -530,7 +548,8 @@ void launch_runs(const Index &ix, const Batch &b, uint64_t n, uint32_t nt, const
                  CellT *cells, hipStream_t s) {
     const uint32_t Bp = (ix.p.B + 3) & ~3u;
     hipLaunchKernelGGL((short_runs_kernel<CellT, RP, COUNT>), dim3(blocks_for(n, RUN_TILE), nt),
-                       dim3(256), 0, s, b.pairs, n, grp, ix.p.R, Bp, b.pos, b.longs, b.nlong, cells);
+                       dim3(256), 0, s, b.pairs, n, grp, ix.p.R, Bp, b.pos, b.longs, b.nlong,
+                       reinterpret_cast<unsigned long long *>(b.total + 1), cells);
     FL_CHECK_LAUNCH();
     if (n > RUN_SHORT) {
         const uint32_t nwords = (ix.p.R * Bp + 31) / 32;  // at most 128 KiB (R <= 16, B <= 65536)
@@ -546,7 +565,8 @@ void launch_runs(const Index &ix, const Batch &b, uint64_t n, uint32_t nt, const
         const uint64_t most = n * nt / (RUN_SHORT + 1) + 1;
         hipLaunchKernelGGL((long_runs_kernel<CellT, RP, COUNT>),
                            dim3((unsigned)std::min<uint64_t>(most, 2048)), dim3(256), nwords * 4, s,
-                           b.pairs, n, grp, ix.p.R, Bp, nwords, b.longs, b.nlong, b.pos, cells);
+                           b.pairs, n, grp, ix.p.R, Bp, nwords, b.longs, b.nlong, b.pos,
+                           reinterpret_cast<unsigned long long *>(b.total + 1), cells);
         FL_CHECK_LAUNCH();
     }
 }
@@ -612,7 +632,7 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
     const size_t o_pairs = piece((size_t)bt * n * 8), o_tmp = piece((size_t)stn * n * 8);
     const size_t o_pos = piece((size_t)bt * n * 4);
     const size_t o_longs = piece((size_t)bt * (n / (RUN_SHORT + 1) + 1) * 8);
-    const size_t o_nlong = piece(4), o_ts = piece((bt + 1) * 8);
+    const size_t o_nlong = piece(4), o_ts = piece((bt + 1) * 8), o_total = piece(16);
     const size_t o_blo = piece((size_t)bt * (nblk + 1) * 8);
     const size_t o_ps = piece(pair_sort_scratch_bytes(n, stn));
     const size_t o_scan = piece(scan_scratch_bytes((uint64_t)bt * n));
@@ -620,8 +640,12 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
     char *w = ws.as<char>();
     const Batch b{reinterpret_cast<uint64_t *>(w + o_pairs), reinterpret_cast<uint32_t *>(w + o_pos),
                   reinterpret_cast<uint64_t *>(w + o_longs), reinterpret_cast<unsigned int *>(w + o_nlong),
-                  reinterpret_cast<uint64_t *>(w + o_ts), reinterpret_cast<uint64_t *>(w + o_blo)};
+                  reinterpret_cast<uint64_t *>(w + o_ts), reinterpret_cast<uint64_t *>(w + o_total),
+                  reinterpret_cast<uint64_t *>(w + o_blo)};
     uint64_t *tmp = reinterpret_cast<uint64_t *>(w + o_tmp);
+    hipLaunchKernelGGL(zero_tail_kernel, dim3(1), dim3(64), 0, s,
+                       reinterpret_cast<unsigned char *>(b.total), 0ull, 16ull);
+    FL_CHECK_LAUNCH();
     for (uint32_t t0 = 0; t0 < L; t0 += bt) {
         const uint32_t nt = std::min(bt, L - t0);
         // codes by table (in the counts' place), sorted points
@@ -636,12 +660,12 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
                            reinterpret_cast<unsigned char *>(b.nlong), 0ull, 4ull);
         FL_CHECK_LAUNCH();
         runs<uint16_t, true>(ix, b, n, nt, grp, nullptr, s);
-        device_exclusive_scan_u32(b.pos, (uint64_t)nt * n, out.entries, b.tstart + nt, w + o_scan, s);
-        uint64_t total = 0;
-        FL_HIP(hipMemcpyAsync(&total, b.tstart + nt, 8, hipMemcpyDeviceToHost, s));
+        device_exclusive_scan_u32(b.pos, (uint64_t)nt * n, out.entries, b.total, w + o_scan, s);
+        uint64_t got[2] = {0, 0};
+        FL_HIP(hipMemcpyAsync(got, b.total, 16, hipMemcpyDeviceToHost, s));
         // offsets (queued before the total is waited for)
-        hipLaunchKernelGGL(table_starts_kernel, dim3(blocks_for(nt, 64)), dim3(64), 0, s, b.pos, n, nt,
-                           b.tstart);
+        hipLaunchKernelGGL(table_starts_kernel, dim3(blocks_for(nt + 1, 64)), dim3(64), 0, s, b.pos, n,
+                           nt, b.total, b.tstart);
         FL_CHECK_LAUNCH();
         hipLaunchKernelGGL(bucket_blocks_kernel, dim3(blocks_for(nblk + 1, 256), nt), dim3(256), 0, s,
                            b.pairs, n, nbk, nblk, b.blo);
@@ -651,6 +675,8 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
                            static_cast<uint32_t *>(offsets.get()) + (uint64_t)t0 * (nbk + 1));
         FL_CHECK_LAUNCH();
         FL_HIP(hipStreamSynchronize(s));
+        const uint64_t total = got[0];
+        out.mean_entries = (double)got[1] / (double)n;
         if (total > 0xFFFFFFFFull) fail(FLINNG_EINVAL, "reverse index exceeds 2^32 entries");
         const uint64_t here = total - out.entries;
         parts.emplace_back(cells_with_tail(here, csz, s), here);

@@ -1,4 +1,6 @@
-// Batched FLINNG query on gfx950: count, threshold, decode.
+// Batched FLINNG query on gfx950: count, threshold, decode (the general kernel;
+// query_sparse.hip serves indexes whose queries touch few cells and leaves the
+// queries it cannot take to this one).
 //
 // One workgroup owns one query at a time (a persistent grid pulls queries
 // from a device counter).  All per-query state lives in LDS:
@@ -28,7 +30,7 @@
 
 #include <algorithm>
 
-#include "flinng_internal.h"
+#include "query_common.h"
 
 namespace flinng {
 
@@ -47,41 +49,15 @@ constexpr uint32_t HC_MAX = 32;
 // the 5M URL and configured genome indexes for sparse, 8192-65536 tried.)
 constexpr uint32_t BUDGET_DENSE = 4096, BUDGET_SPARSE = 32768;
 // positive-cell list capacity (at least one round of T cells)
-__host__ __device__ constexpr uint32_t cl_for(int T) { return T <= 256 ? 256u : 1024u; }
+// (16-bit entries: a group id is below 2^16; general k: one round exactly)
+__host__ __device__ constexpr uint32_t cl_for(int T, bool gk) { return gk ? (uint32_t)T : 2u * T; }
 // capacity of the list of cells a sparse query touched (fast path)
 __host__ __device__ constexpr uint32_t tl_for(int T) { return (uint32_t)T; }
-
-struct QArgs {
-    const uint32_t *codes;
-    uint64_t nq;
-    const uint32_t *offsets;
-    const void *cells;
-    const uint32_t *mem;   // [R][B][mstride] member ids
-    const uint16_t *cmg;   // [R][B][mstride][Rp] member group rows
-    const uint32_t *cfl;   // [R][B][mstride] groups in repetitions r+1, r+2
-    uint64_t N;
-    const uint32_t *gsize; // [R][B] members of each cell
-    uint32_t gmax;         // the largest cell
-    uint32_t L, R, Rp, B, Bp, nbits, k, cap;
-    uint32_t mstride;      // member slots per cell (multiple of 4)
-    uint32_t threads;      // workgroup size the kernel is launched with
-    uint32_t hc;           // histogram copies (a power of two)
-    float inv_bp;          // 1 / Bp, for cell id -> repetition
-    uint32_t *ids;
-    uint32_t *scores;
-    uint8_t *counts_out;   // debug: write counters and skip decode
-    uint32_t *work;        // persistent: next query counter (nullptr: 1 WG/query)
-    uint32_t budget;
-    unsigned long long *stats;  // optional per-launch totals: list entries read,
-                                // members read (all passes), members read in
-                                // final passes, passes, group rows read in
-                                // final passes
-};
 
 struct QLayout {
     uint32_t cnt_words, hist_words, cap;
     size_t off_cnt, off_hist, off_pre, off_pree, off_start, off_end, off_buf, off_lb, off_lp, off_tl,
-        off_fp, off_fs, off_misc, total;
+        off_wq, off_misc, total;
 };
 
 // gk: the general-k decode, which also needs the per-thread prefix slots.
@@ -98,65 +74,15 @@ __host__ __device__ inline QLayout q_layout(uint32_t L, uint32_t R, uint32_t Bp,
     l.off_pree = o;  o += (size_t)(L + 1) * 4;
     l.off_start = o; o += (size_t)L * 4;
     l.off_end = o;   o += (size_t)L * 4;
-    l.off_lb = o;    o += cl_for(T) * 4;
+    l.off_lb = o;    o += cl_for(T, gk) * 2;
     l.off_lp = o;    o += gk ? (size_t)T * 4 : 0;
     l.off_tl = o;    o += gk ? 0 : (size_t)tl_for(T) * 4;
-    // the flattened walk of the 1024-thread fast path: 4-rounded prefix
-    // sums and sizes of the listed cells
-    const bool flat = !gk && T == 1024;
-    l.off_fp = o;    o += flat ? (size_t)(cl_for(T) + 1) * 4 : 0;
-    l.off_fs = o;    o += flat ? (size_t)cl_for(T) * 4 : 0;
+    // the wavefronts' survivor queues (1024-thread fast path)
+    l.off_wq = o;    o += !gk && T == 1024 ? (size_t)(T / 64) * WALK_QUEUE * 4 : 0;
     l.off_misc = o;  o += 64 * 4;
     l.off_hist = o;  o += (size_t)l.hist_words * 4;  // last: only its size varies with hc
     l.total = (o + 15) & ~(size_t)15;
     return l;
-}
-
-// misc slots
-enum { M_Q = 0, M_BUFN, M_NGE, M_NALL, M_LEVEL, M_REP, M_KEEPALL, M_NEXT, M_THRLO,
-       M_THRHI, M_LCNT, M_MEMB, M_THI, M_ST_ALL, M_ST_FINAL, M_ST_PASSES, M_NT, M_GATH,
-       M_ST_GATH, M_SCAN0 };
-
-// c / d for c < 2^24 and d >= 1, from the float quotient (within one of the
-// true quotient: c is exact in float and the two roundings of c * (1/d)
-// perturb it by less than one for d >= 2; d = 1 is exact) and one correction.
-// A copy of a lane-dependent value that the compiler cannot merge with the
-// original: an LDS address derived from it is then recomputed where it is
-// used instead of being kept live (and spilled) across the whole query.
-__device__ inline uint32_t fresh_copy(uint32_t x) {
-    uint32_t y;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(y) : "v"(x));
-    return y;
-}
-
-__device__ inline uint32_t div_small(uint32_t c, uint32_t d, float inv) {
-    uint32_t q = (uint32_t)((float)c * inv);
-    const int32_t rr = (int32_t)(c - q * d);
-    return rr < 0 ? q - 1 : (rr >= (int32_t)d ? q + 1 : q);
-}
-
-template <int T>
-__device__ inline uint32_t wg_excl_scan(uint32_t v, uint32_t *scr, uint32_t *total) {
-    constexpr int TW = T / 64;
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) scr[wave] = inc;
-    __syncthreads();
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < TW; ++w) {
-        uint32_t c = scr[w];
-        pre += (w < wave) ? c : 0u;
-        tot += c;
-    }
-    __syncthreads();
-    *total = tot;
-    return pre + inc - v;
 }
 
 // Bitonic sort of buf[0, cap) ascending (cap a power of two).
@@ -177,174 +103,6 @@ __device__ inline void wg_bitonic(uint64_t *buf, uint32_t cap) {
             __syncthreads();
         }
     }
-}
-
-__device__ inline uint64_t shfl64(uint64_t v, int src) {
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src, 64);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(v >> 32), src, 64);
-    return ((uint64_t)hi << 32) | lo;
-}
-__device__ inline uint64_t shfl64_up1(uint64_t v) {
-    const uint32_t lo = (uint32_t)__shfl_up((int)(uint32_t)v, 1, 64);
-    const uint32_t hi = (uint32_t)__shfl_up((int)(uint32_t)(v >> 32), 1, 64);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// Per-wavefront decode state: its top-k list (lane i holds the i-th smallest
-// key), the k-th key, and tallies (uniform across the wavefront).
-struct WaveState {
-    uint64_t wl, kth;
-    uint32_t n_ge, n_all, members, gathered;
-};
-
-// Broadcast a 64-bit value from one lane (src uniform across the wavefront).
-__device__ inline uint64_t bcast64(uint64_t v, int src) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, src);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), src);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// The value of lane (lane ^ J) (every lane active): quad permutations and a
-// row rotation by 8 move data within the VALU (DPP); the other distances go
-// through the LDS crossbar (swizzle within 32 lanes, permute across halves).
-template <int J>
-__device__ inline uint32_t lane_xor(uint32_t v, int lane) {
-    if constexpr (J == 1) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // quad [1,0,3,2]
-    } else if constexpr (J == 2) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // quad [2,3,0,1]
-    } else if constexpr (J == 8) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, false);  // row rotate 8
-    } else if constexpr (J < 32) {
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (J << 10) | 0x1F);  // xor J, 32-lane groups
-    } else {
-        return (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ J) << 2, (int)v);
-    }
-}
-
-// One compare-exchange step of a bitonic sort across the wavefront: lanes
-// l and l ^ J exchange so that the lower lane keeps the smaller key in
-// ascending blocks (bit S of l clear) and the larger one in descending
-// blocks.
-// Lanes l of a wavefront with bit S of l equal to bit J of l, as a mask
-// (a compile-time constant, rematerialised where it is used).
-constexpr unsigned long long keep_min_mask(int S, int J) {
-    unsigned long long m = 0;
-    for (int l = 0; l < 64; ++l)
-        if (((l & S) == 0) == ((l & J) == 0)) m |= 1ull << l;
-    return m;
-}
-
-template <int S, int J>
-__device__ inline uint64_t bitonic_step(uint64_t v, int lane) {
-    const uint32_t plo = lane_xor<J>((uint32_t)v, lane);
-    const uint32_t phi = lane_xor<J>((uint32_t)(v >> 32), lane);
-    const uint64_t p = ((uint64_t)phi << 32) | plo;
-    // take the partner's key where it is smaller in a keep-min lane, or
-    // larger in a keep-max lane
-    constexpr unsigned long long km = keep_min_mask(S, J);
-    const unsigned long long take = ~(__ballot(p < v) ^ km);
-    return __builtin_amdgcn_inverse_ballot_w64(take) ? p : v;
-}
-
-// Sort one key per lane ascending across the 64 lanes (every lane active).
-__device__ inline uint64_t wave_sort64(uint64_t v, int lane) {
-    v = bitonic_step<2, 1>(v, lane);
-    v = bitonic_step<4, 2>(v, lane);
-    v = bitonic_step<4, 1>(v, lane);
-    v = bitonic_step<8, 4>(v, lane);
-    v = bitonic_step<8, 2>(v, lane);
-    v = bitonic_step<8, 1>(v, lane);
-    v = bitonic_step<16, 8>(v, lane);
-    v = bitonic_step<16, 4>(v, lane);
-    v = bitonic_step<16, 2>(v, lane);
-    v = bitonic_step<16, 1>(v, lane);
-    v = bitonic_step<32, 16>(v, lane);
-    v = bitonic_step<32, 8>(v, lane);
-    v = bitonic_step<32, 4>(v, lane);
-    v = bitonic_step<32, 2>(v, lane);
-    v = bitonic_step<32, 1>(v, lane);
-    v = bitonic_step<64, 32>(v, lane);
-    v = bitonic_step<64, 16>(v, lane);
-    v = bitonic_step<64, 8>(v, lane);
-    v = bitonic_step<64, 4>(v, lane);
-    v = bitonic_step<64, 2>(v, lane);
-    v = bitonic_step<64, 1>(v, lane);
-    return v;
-}
-
-// Insert the keys of the lanes in `tk` into the wavefront's sorted top-k
-// list, all at once (called with every lane of the wavefront active; keys
-// are distinct).  Into an empty list many candidates are sorted across the
-// wavefront and the first k kept, a few are ranked among themselves and
-// permuted to their ranks.  Otherwise each candidate below the k-th key is
-// broadcast in turn (readlane) and its place in the merged order found by
-// ballot (its rank among the list plus its rank among the candidates); the
-// places taken form a lane mask and each place notes its candidate.  Then
-// each lane pulls its new entry: the candidate's key, or the list entry
-// shifted up by the candidates placed before it.
-__device__ inline bool wave_insert(WaveState &ws, uint64_t key, unsigned long long tk, uint32_t k,
-                                   int lane) {
-    const unsigned long long cm = __ballot(key < ws.kth) & tk;
-    if (!cm) return false;
-    const bool in = __builtin_amdgcn_inverse_ballot_w64(cm);
-    if (bcast64(ws.wl, 0) == ~0ull) {
-        // empty list (keys never equal ~0: their cell field is below 2^24 - 1)
-        const uint32_t c = (uint32_t)__popcll(cm);
-        if (c > 16) {
-            const uint64_t v = wave_sort64(in ? key : ~0ull, lane);
-            ws.wl = ((uint32_t)lane < k) ? v : ~0ull;
-        } else {
-            uint32_t rank = 0;
-            for (unsigned long long m = cm; m; m &= m - 1) {
-                const uint64_t kk = bcast64(key, __ffsll((long long)m) - 1);
-                rank += (kk < key) ? 1u : 0u;
-            }
-            // the other lanes take the places after the candidates, in order
-            const uint32_t dest = in ? rank : c + __builtin_amdgcn_mbcnt_hi(
-                                                     (uint32_t)(~cm >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)~cm, 0u));
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute((int)(dest * 4), (int)(uint32_t)key);
-            const uint32_t hi =
-                (uint32_t)__builtin_amdgcn_ds_permute((int)(dest * 4), (int)(uint32_t)(key >> 32));
-            ws.wl = ((uint32_t)lane < (c < k ? c : k)) ? (((uint64_t)hi << 32) | lo) : ~0ull;
-        }
-        ws.kth = bcast64(ws.wl, (int)k - 1);
-        return true;
-    }
-    unsigned long long placed = 0;  // list places taken by candidates
-    int from = 0;                   // the candidate lane placed at this place
-    for (unsigned long long m = cm; m; m &= m - 1) {
-        const int src = __ffsll((long long)m) - 1;
-        const uint64_t kk = bcast64(key, src);
-        const uint32_t pos = (uint32_t)__popcll(__ballot(ws.wl < kk)) +
-                             (uint32_t)__popcll(__ballot(key < kk) & cm);
-        if (pos < k) {
-            placed |= 1ull << pos;
-            from = (lane == (int)pos) ? src : from;
-        }
-    }
-    // candidates placed before this lane; the list entry that moves here
-    const uint32_t before =
-        __builtin_amdgcn_mbcnt_hi((uint32_t)(placed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)placed, 0u));
-    const int li = lane - (int)before;
-    const bool fromc = __builtin_amdgcn_inverse_ballot_w64(placed);
-    const uint32_t clo = (uint32_t)__shfl((int)(uint32_t)key, from, 64);
-    const uint32_t chi = (uint32_t)__shfl((int)(uint32_t)(key >> 32), from, 64);
-    const uint32_t llo = (uint32_t)__shfl((int)(uint32_t)ws.wl, li, 64);
-    const uint32_t lhi = (uint32_t)__shfl((int)(uint32_t)(ws.wl >> 32), li, 64);
-    const uint64_t v = fromc ? (((uint64_t)chi << 32) | clo) : (((uint64_t)lhi << 32) | llo);
-    ws.wl = ((uint32_t)lane < k) ? v : ~0ull;
-    ws.kth = bcast64(ws.wl, (int)k - 1);
-    return true;
-}
-
-// Compare-exchange of two keys held by the same lane (ascending).
-__device__ inline void ce64(uint64_t &a, uint64_t &b) {
-    const bool sw = b < a;
-    const uint64_t lo = sw ? b : a, hi = sw ? a : b;
-    a = lo;
-    b = hi;
 }
 
 // Load the group rows of 4 consecutive member slots (4*RP uint16, 16-byte
@@ -391,7 +149,7 @@ __device__ inline uint32_t lds_u8_at(uint32_t addr) {
 // item past the last, read the cell's first slots and are marked invalid), so
 // that all U items' loads are issued before any of them is waited on.
 template <int RP, int U, int T>
-__device__ inline void walk_cells(const uint32_t *lbs, uint32_t nl, const uint32_t *__restrict__ memr,
+__device__ inline void walk_cells(const uint16_t *lbs, uint32_t nl, const uint32_t *__restrict__ memr,
                                   const uint16_t *__restrict__ cmgr, const uint8_t *cnt8, uint32_t R,
                                   uint32_t Bp, uint32_t mstride, uint32_t level, bool keep,
                                   const uint32_t *__restrict__ gsz, uint32_t cpc, uint32_t k, int lane,
@@ -489,29 +247,6 @@ __device__ inline void walk_cells(const uint32_t *lbs, uint32_t nl, const uint32
     }
 }
 
-// The group row of one member slot (RP uint16) as (RP + 1) / 2 dwords.
-template <int RP>
-__device__ inline void load_row1(const uint16_t *p, uint32_t (&w)[(RP + 1) / 2]) {
-    if constexpr (RP == 1) {
-        w[0] = *p;
-    } else if constexpr (RP == 2) {
-        w[0] = *reinterpret_cast<const uint32_t *>(p);
-    } else if constexpr (RP == 4) {
-        const uint2 v = *reinterpret_cast<const uint2 *>(p);
-        w[0] = v.x;
-        w[1] = v.y;
-    } else {
-#pragma unroll
-        for (int i = 0; i < RP / 8; ++i) {
-            const uint4 v = reinterpret_cast<const uint4 *>(p)[i];
-            w[4 * i + 0] = v.x;
-            w[4 * i + 1] = v.y;
-            w[4 * i + 2] = v.z;
-            w[4 * i + 3] = v.w;
-        }
-    }
-}
-
 // walk_cells for a pass that keeps only keys with m >= level (R >= 2): a
 // member's m is at most its counts in repetitions r+1 and r+2 (mod R), read
 // from the 4-byte filter word of its slot, so each lane first reads the
@@ -524,7 +259,7 @@ __device__ inline void load_row1(const uint16_t *p, uint32_t (&w)[(RP + 1) / 2])
 // member with m >= level survives the filter, so the keys offered to the
 // top-k, and the tallies, are those of walk_cells.
 template <int RP, int U, int T>
-__device__ inline void walk_cells_filtered(const uint32_t *lbs, uint32_t nl,
+__device__ inline void walk_cells_filtered(const uint16_t *lbs, uint32_t nl,
                                            const uint32_t *__restrict__ memr,
                                            const uint16_t *__restrict__ cmgr,
                                            const uint32_t *__restrict__ cflr, uint32_t R, uint32_t Bp,
@@ -610,93 +345,6 @@ __device__ inline void walk_cells_filtered(const uint32_t *lbs, uint32_t nl,
     }
 }
 
-// walk_cells_filtered over the listed cells' members as one flattened
-// sequence (each cell's run padded to a multiple of 4 inside its stride):
-// items of 256 consecutive positions, so that a wavefront's lanes stay busy
-// however the cell sizes fall (cells of 122 members would leave half the
-// lanes of a per-cell item idle, cells of 305 a second item nearly empty).
-// A lane finds the cell of its 4 positions by a binary search over the
-// prefix sums fp (LDS), then reads their filter words; survivors as in
-// walk_cells_filtered.
-template <int RP, int U, int T>
-__device__ inline void walk_flat_filtered(const uint32_t *lbs, const uint32_t *fp, const uint32_t *fs,
-                                          uint32_t nl, uint32_t total,
-                                          const uint32_t *__restrict__ memr,
-                                          const uint16_t *__restrict__ cmgr,
-                                          const uint32_t *__restrict__ cflr, uint32_t R, uint32_t Bp,
-                                          uint32_t mstride, uint32_t level, uint32_t f1b, uint32_t f2b,
-                                          uint32_t k, int lane, int wave, WaveState &ws) {
-    constexpr int TW = T / 64;
-    constexpr int RW = (RP + 1) / 2;
-    const uint32_t nitems = (total + 255) / 256;
-    const uint32_t wv = __builtin_amdgcn_readfirstlane(wave);
-    const uint32_t lim = 256u - level;
-    uint32_t rb[RP];
-#pragma unroll
-    for (int r = 0; r < RP; ++r) rb[r] = ((uint32_t)r < R ? (uint32_t)r : R - 1) * Bp;
-    for (uint32_t i0 = wv; i0 < nitems; i0 += TW * U) {
-        uint4 fv[U];
-        uint32_t slot[U];  // within the repetition: B * mstride < 2^32
-        uint32_t nv[U];
-#pragma unroll
-        for (int g = 0; g < U; ++g) {
-            const uint32_t i = i0 + (uint32_t)g * TW;
-            const uint32_t pos = i * 256 + 4 * lane;
-            const bool valid = i < nitems && pos < total;
-            const uint32_t pp = valid ? pos : 0u;
-            uint32_t lo = 0, hi = nl;  // the last cell whose run starts at or before pp
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (fp[mid] <= pp) lo = mid; else hi = mid;
-            }
-            const uint32_t o = pp - fp[lo], sz = fs[lo];
-            nv[g] = (valid && o < sz) ? ((sz - o < 4) ? sz - o : 4u) : 0u;
-            slot[g] = lbs[lo] * mstride + o;
-            fv[g] = *reinterpret_cast<const uint4 *>(cflr + slot[g]);
-        }
-        uint32_t pend = 0;
-#pragma unroll
-        for (int g = 0; g < U; ++g) {
-            const uint32_t fw[4] = {fv[g].x, fv[g].y, fv[g].z, fv[g].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                ws.members += (uint32_t)__popcll(__ballot((uint32_t)e < nv[g]));
-                const uint32_t b1 = lds_u8_at(f1b + (fw[e] & 0xFFFFu));
-                const uint32_t b2 = lds_u8_at(f2b + (fw[e] >> 16));
-                if ((uint32_t)e < nv[g] && b1 < lim && b2 < lim) pend |= 1u << (4 * g + e);
-            }
-        }
-        while (__ballot(pend != 0)) {
-            const bool act = pend != 0;
-            const uint32_t m = act ? (uint32_t)__builtin_ctz(pend) : 0u;
-            pend &= pend - 1;
-            uint32_t sl = slot[0];
-#pragma unroll
-            for (int g = 1; g < U; ++g) sl = (m >> 2) == (uint32_t)g ? slot[g] : sl;
-            sl += m & 3u;
-            uint32_t xid = 0, rw[RW];
-#pragma unroll
-            for (int i = 0; i < RW; ++i) rw[i] = 0;
-            if (act) {
-                xid = memr[sl];
-                load_row1<RP>(cmgr + (uint64_t)sl * RP, rw);
-            }
-            ws.gathered += (uint32_t)__popcll(__ballot(act));
-            uint32_t t = 0;
-#pragma unroll
-            for (int r = 0; r < RP; ++r) {
-                const uint32_t c = rb[r] + ((rw[r >> 1] >> (16 * (r & 1))) & 0xFFFFu);
-                const uint32_t tv = (lds_u8_at(c) << 24) | c;
-                t = tv > t ? tv : t;
-            }
-            const unsigned long long gm = __ballot(act && t < (lim << 24));
-            ws.n_ge += (uint32_t)__popcll(gm);
-            ws.n_all += (uint32_t)__popcll(gm);
-            wave_insert(ws, ((uint64_t)t << 32) | xid, gm, k, lane);
-        }
-    }
-}
-
 // General k: the members of the listed cells as one flattened sequence (lps:
 // the cells' exclusive size sums), V positions per thread and round, kept keys
 // below the threshold appended to the LDS buffer.  Where the pass filters, a
@@ -711,7 +359,7 @@ struct AppendState {
 };
 
 template <int RP, int T>
-__device__ inline void walk_append(const uint32_t *lbs, const uint32_t *lps, uint32_t nl, uint32_t total,
+__device__ inline void walk_append(const uint16_t *lbs, const uint32_t *lps, uint32_t nl, uint32_t total,
                                    const uint32_t *__restrict__ memr, const uint16_t *__restrict__ cmgr,
                                    const uint32_t *__restrict__ cflr, uint32_t R, uint32_t Bp,
                                    uint32_t mstride, uint32_t level, bool keep, bool filt, uint32_t f1b,
@@ -817,7 +465,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     extern __shared__ __align__(16) unsigned char lds[];
     const uint32_t HC = A.hc;
     const QLayout lay = q_layout(A.L, A.R, A.Bp, A.cap, QT, HC, GK);
-    constexpr uint32_t CL = cl_for(QT);
+    constexpr uint32_t CL = cl_for(QT, GK);
     uint64_t *buf = reinterpret_cast<uint64_t *>(lds + lay.off_buf);
     uint32_t *cnt32 = reinterpret_cast<uint32_t *>(lds + lay.off_cnt);
     const uint8_t *cnt8 = lds + lay.off_cnt;
@@ -826,7 +474,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     uint32_t *pree = reinterpret_cast<uint32_t *>(lds + lay.off_pree);
     uint32_t *lstart = reinterpret_cast<uint32_t *>(lds + lay.off_start);
     uint32_t *lend = reinterpret_cast<uint32_t *>(lds + lay.off_end);
-    uint32_t *lb = reinterpret_cast<uint32_t *>(lds + lay.off_lb);
+    uint16_t *lb = reinterpret_cast<uint16_t *>(lds + lay.off_lb);
     uint32_t *lp = reinterpret_cast<uint32_t *>(lds + lay.off_lp);
     uint32_t *tl = reinterpret_cast<uint32_t *>(lds + lay.off_tl);
     constexpr uint32_t TLC = tl_for(QT);
@@ -842,12 +490,29 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     const CellT *cells = static_cast<const CellT *>(A.cells);
 
     uint64_t q = blockIdx.x;
+    // the sparse kernel's deferred queries: workgroup w looks through queries
+    // w, w + grid, ..., 64 at a time (each wavefront reads the 64 marks)
+    uint64_t dbase = blockIdx.x;
+    unsigned long long dmask = 0;
     for (;;) {
         if constexpr (PERS) {
-            if (tid == 0) misc[M_Q] = atomicAdd(A.work, 1u);
-            __syncthreads();
-            q = misc[M_Q];
-            __syncthreads();
+            if (A.deferred) {
+                while (!dmask && dbase < A.nq) {
+                    const uint64_t mine = dbase + (uint64_t)lane * gridDim.x;
+                    dmask = __ballot(mine < A.nq && A.ids[mine * k] == DEFERRED);
+                    if (!dmask) dbase += 64ull * gridDim.x;
+                }
+                if (!dmask) break;
+                q = dbase + (uint64_t)(__ffsll((long long)dmask) - 1) * gridDim.x;
+                dmask &= dmask - 1;
+                if (!dmask) dbase += 64ull * gridDim.x;
+                __syncthreads();  // every wavefront has its marks before any is overwritten
+            } else {
+                if (tid == 0) misc[M_Q] = atomicAdd(A.work, 1u);
+                __syncthreads();
+                q = misc[M_Q];
+                __syncthreads();
+            }
         }
         if (q >= A.nq) break;
 
@@ -1165,8 +830,8 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
 
           if constexpr (!GK) {
             // Fast decode (k <= 64): the positive cells of `rep` go into an
-            // LDS list (one word-wide scan, or 256 cells at a time when they
-            // do not fit); each wavefront streams (cell, 256-member chunk)
+            // LDS list (one word-wide scan, or at least QT cells at a time when
+            // they do not fit); each wavefront streams (cell, 256-member chunk)
             // items with several in flight per lane and keeps its own top-k
             // in registers; the lists are merged by rank at the end.
             WaveState ws{~0ull, ~0ull, 0u, 0u, 0u, 0u};
@@ -1176,8 +841,27 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
             // the filtered walk: a pass keeping only m >= level, R >= 2
             constexpr int WF = (QT == 256 || PERS) ? (WAVES >= 8 ? 1 : 2) : 4;
             const bool filt = !keep && R >= 2 && rstride < (1ull << 32);  // 32-bit slots
+            // walk_items: filter items in flight per lane; items are divided
+            // by cpc exactly up to 2^32 / cpc of them
             const uint32_t *cflr = A.cfl + rep * rstride;
             const uint32_t f1b = ((rep + 1) % R) * Bp, f2b = ((rep + 2) % R) * Bp;
+            constexpr int WI = PERS ? 2 : 4;
+            const bool items_ok = gmax <= 65536u;
+            auto walk_wide = [&](uint32_t nl) __attribute__((always_inline)) {
+                uint32_t *wq = reinterpret_cast<uint32_t *>(lds + lay.off_wq) + wave * WALK_QUEUE;
+                const uint32_t lim = 256u - level;
+                walk_items<RP, QW, WI>(
+                    lb, nl, memr, cmgr, cflr, R, Bp, A, level, false, wq, lane, wave, ws,
+                    [&](uint32_t w) {
+                        return lds_u8_at(f1b + (w & 0xFFFFu)) < lim && lds_u8_at(f2b + (w >> 16)) < lim;
+                    },
+                    [&](uint32_t r, uint32_t b) { return lds_u8_at(r * Bp + b); });
+                if (A.stats) {  // members of the listed cells
+                    uint32_t n = 0;
+                    for (uint32_t i = tid; i < nl; i += QT) n += A.gsize[rep * B + lb[i]];
+                    atomicAdd(&misc[M_MEMB], n);
+                }
+            };
             const uint32_t nrep = hist[rep * (L + 1) + level];
             if (nrep <= CL) {
                 const uint32_t nt = misc[M_NT];
@@ -1186,7 +870,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                     const uint32_t c0 = rep * Bp;
                     for (uint32_t i = tid; i < nt; i += QT) {
                         const uint32_t c = tl[i];
-                        if (c - c0 < B && 255u - cnt8[c] >= level) lb[atomicAdd(&misc[M_LCNT], 1u)] = c - c0;
+                        if (c - c0 < B && 255u - cnt8[c] >= level) lb[atomicAdd(&misc[M_LCNT], 1u)] = (uint16_t)(c - c0);
                     }
                 } else {
                     for (uint32_t w = tid; w < Bp / 4; w += QT) {
@@ -1196,30 +880,16 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                         for (int j = 0; j < 4; ++j) {
                             const uint32_t b = 4 * w + j;
                             if (b < B && ((v >> (8 * j)) & 255u) >= level)
-                                lb[atomicAdd(&misc[M_LCNT], 1u)] = b;
+                                lb[atomicAdd(&misc[M_LCNT], 1u)] = (uint16_t)b;
                         }
                     }
                 }
                 __syncthreads();
-                if (QT == 1024 && filt) {
-                    // sizes and 4-rounded prefix sums of the listed cells
-                    // (nrep <= CL = QT: one cell per thread)
-                    uint32_t *fp = reinterpret_cast<uint32_t *>(lds + lay.off_fp);
-                    uint32_t *fs = reinterpret_cast<uint32_t *>(lds + lay.off_fs);
-                    const uint32_t csz = (uint32_t)tid < nrep ? A.gsize[rep * B + lb[tid]] : 0u;
-                    uint32_t ftot;
-                    const uint32_t fex = wg_excl_scan<QT>((csz + 3) & ~3u, scr, &ftot);
-                    if ((uint32_t)tid < nrep) {
-                        fp[tid] = fex;
-                        fs[tid] = csz;
-                    }
-                    __syncthreads();
-                    walk_flat_filtered<RP, WF, QT>(lb, fp, fs, nrep, ftot, memr, cmgr, cflr, R, Bp,
-                                                   A.mstride, level, f1b, f2b, k, lane, wave, ws);
+                if (QT == 1024 && filt && items_ok) {
+                    if constexpr (QT == 1024) walk_wide(nrep);
                 } else if (filt)
-                    walk_cells_filtered<RP, WF, QT>(lb, nrep, memr, cmgr, cflr, R, Bp, A.mstride,
-                                                    level, f1b, f2b, A.gsize + rep * B, cpc, k, lane,
-                                                    wave, ws);
+                    walk_cells_filtered<RP, WF, QT>(lb, nrep, memr, cmgr, cflr, R, Bp, A.mstride, level, f1b, f2b,
+                                                    A.gsize + rep * B, cpc, k, lane, wave, ws);
                 else
                     walk_cells<RP, WU, QT>(lb, nrep, memr, cmgr, cnt8, R, Bp, A.mstride, level, keep,
                                            A.gsize + rep * B, cpc, k, lane, wave, ws);
@@ -1232,17 +902,18 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                     uint32_t wbase = 0;
                     if (lane == 0 && pm) wbase = atomicAdd(&misc[M_LCNT], (uint32_t)__popcll(pm));
                     wbase = (uint32_t)__shfl((int)wbase, 0, 64);
-                    if (pos) lb[wbase + (uint32_t)__popcll(pm & ltmask)] = b;
+                    if (pos) lb[wbase + (uint32_t)__popcll(pm & ltmask)] = (uint16_t)b;
                     __syncthreads();
                     const uint32_t nl = misc[M_LCNT];
                     if (nl > CL - QT || cb0 + QT >= B) {
-                        if (filt)
-                            walk_cells_filtered<RP, WF, QT>(lb, nl, memr, cmgr, cflr, R, Bp,
-                                                            A.mstride, level, f1b, f2b,
+                        if (QT == 1024 && filt && items_ok) {
+                            if constexpr (QT == 1024) walk_wide(nl);
+                        } else if (filt)
+                            walk_cells_filtered<RP, WF, QT>(lb, nl, memr, cmgr, cflr, R, Bp, A.mstride, level, f1b, f2b,
                                                             A.gsize + rep * B, cpc, k, lane, wave, ws);
                         else
-                            walk_cells<RP, WU, QT>(lb, nl, memr, cmgr, cnt8, R, Bp, A.mstride, level,
-                                                   keep, A.gsize + rep * B, cpc, k, lane, wave, ws);
+                            walk_cells<RP, WU, QT>(lb, nl, memr, cmgr, cnt8, R, Bp, A.mstride, level, keep,
+                                                   A.gsize + rep * B, cpc, k, lane, wave, ws);
                         __syncthreads();
                         if (tid == 0) misc[M_LCNT] = 0;
                         __syncthreads();
@@ -1326,7 +997,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                     for (int j = 0; j < 4; ++j) {
                         const uint32_t b = 4 * w + j;
                         if (b < B && ((v >> (8 * j)) & 255u) >= level)
-                            lb[atomicAdd(&misc[M_LCNT], 1u)] = b;
+                            lb[atomicAdd(&misc[M_LCNT], 1u)] = (uint16_t)b;
                     }
                 }
                 __syncthreads();
@@ -1341,7 +1012,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                     wbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)wbase);
                     if (pos)
                         lb[wbase + __builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u))] = b;
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u))] = (uint16_t)b;
                     __syncthreads();
                     const uint32_t nl = misc[M_LCNT];
                     if (nl > CL - QT || cb0 + QT >= B) {
@@ -1571,7 +1242,10 @@ template <typename CellT, int RP, int QT, bool GK>
 static void launch_rp(const QArgs &a, size_t lds, bool persistent, hipStream_t s) {
     uint64_t grid = a.nq;
     if (persistent) {
-        const uint64_t per_cu = std::max<uint64_t>(
+        // deferred queries: few but long, so two workgroups per compute unit
+        // in turn rather than one that may find several (URL strings, 21 of
+        // 10,000 deferred: 216 us against 281)
+        const uint64_t per_cu = a.deferred ? 2 : std::max<uint64_t>(
             1, std::min<uint64_t>(8, (uint64_t)(160 * 1024) / std::max<size_t>(lds, 1)));
         grid = std::min<uint64_t>(a.nq, per_cu * (uint64_t)num_cus());
     }
@@ -1651,6 +1325,7 @@ static QArgs make_args(const Index &ix, const uint32_t *codes, uint64_t nq, uint
     a.hc = sh.hc;
     a.mstride = ix.mstride;
     a.inv_bp = 1.0f / (float)a.Bp;
+    set_walk_items(a);
     a.budget = sparse_index(ix) ? BUDGET_SPARSE : BUDGET_DENSE;
     return a;
 }
@@ -1662,15 +1337,20 @@ void query_launch(const Index &ix, const uint32_t *codes_dev, uint64_t nq, uint3
     QArgs a = make_args(ix, codes_dev, nq, k);
     a.ids = ids_dev;
     a.scores = scores_dev;
-    a.work = persistent ? work_counter : nullptr;
     a.stats = stats;
     const size_t lds = q_layout(a.L, a.R, a.Bp, a.cap, (int)a.threads, a.hc, a.k > 64).total;
     if ((int)lds > max_lds())
         fail(FLINNG_EINVAL, "per-query state (" + std::to_string(lds) +
                                 " bytes) exceeds the workgroup LDS limit; reduce B*R or k");
+    if (const int v = sparse_variant(ix, a)) {
+        sparse_query_launch(ix, v, a, s);
+        a.deferred = true;
+        persistent = true;
+    }
     // the persistent grid's query counter starts at 0 (cleared by a kernel,
     // so that the launch can be captured into a graph)
-    if (persistent) {
+    a.work = persistent ? work_counter : nullptr;
+    if (persistent && !a.deferred) {
         hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, work_counter);
         FL_CHECK_LAUNCH();
     }

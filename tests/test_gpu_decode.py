@@ -43,3 +43,46 @@ def test_general_k_equals_oracle(fl, N, R, B, K, L):
             got = gi.query(Q, k, persistent=pers)
             assert np.array_equal(got[0], want[0]), (k, pers)
             assert np.array_equal(got[1], want[1]), (k, pers)
+
+
+def _sets(vals):
+    return np.asarray(vals, dtype=np.uint32), np.arange(len(vals) + 1, dtype=np.uint64)
+
+
+@pytest.mark.parametrize("R,B,L", [
+    (4, 1000, 8),    # 128 threads; Bp is no multiple of 32
+    (2, 37, 70),     # L > 64; cells of 160 members
+    (16, 33, 8),     # a word and a bit per repetition
+    (1, 500, 40),    # nothing to filter by
+    (8, 5000, 60),   # 1024-thread grid, 16-bit cells
+    (5, 14000, 30),  # 1024-thread grid, 32-bit cells, one member in most cells
+])
+def test_sparse_and_deferred_queries_equal_oracle(fl, R, B, L):
+    """Sets of one item each, so that a query meets exactly its copies' cells
+    in every table: most have a few copies, some so many that their entries
+    pass the sparse kernel's limit and the general kernel takes over, and some
+    queries have none (zero-count completion). Also after an insert, whose
+    cells differ in size."""
+    rng = np.random.default_rng(R * 77 + B)
+    n = 20000 if B > 2000 else 6000
+    vals = rng.integers(0, n // 3, n).astype(np.uint64)
+    for j in range(3):
+        vals[rng.permutation(n)[:1500 // (L // 8 + R) + 40]] = 10**6 + j
+    vals = vals * 2654435761 % 2**32
+    n0 = n - 57
+    gi = fl.Index(_sets(vals[:n0]), fl.MINHASH_U32, 1, L, R, B, seed=3, bucket_bits=20)
+    oi = oracle.OracleIndex(oracle.MINHASH_U32, _sets(vals[:n0]), 1, L, R, B, 3, bucket_bits=20)
+    q = np.concatenate([rng.choice(vals, 150), (10**6 + np.arange(3)) * 2654435761 % 2**32,
+                        rng.integers(2**31, 2**32, 20).astype(np.uint64)])
+    reps = 4200 // len(q) + 1  # a batch that fills the chip
+    log("sparse", R, B, L, "entries", gi.info.list_entries)
+    for step in range(2):
+        for k in (1, 10, 64):
+            want = oi.query(_sets(q), k)
+            for pers in (False, True):
+                got = gi.query(_sets(np.tile(q, reps)), k, persistent=pers)
+                assert np.array_equal(got[0], np.tile(want[0], (reps, 1))), (step, k, pers)
+                assert np.array_equal(got[1], np.tile(want[1], (reps, 1))), (step, k, pers)
+        if step == 0:
+            gi.insert(_sets(vals[n0:]))
+            oi.insert(_sets(vals[n0:]))
