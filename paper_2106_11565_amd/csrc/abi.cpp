@@ -145,7 +145,7 @@ const char *flinng_last_error(void) { return g_err.c_str(); }
 }  // extern "C"
 
 static void build_impl(const flinng_params *p, const flinng_input *data, hipStream_t s,
-                       flinng_index **out) {
+                       flinng_index **out, const TextSource *text = nullptr) {
     require(p && data && out, "NULL argument");
     *out = nullptr;
     validate_input(data, p->family, "data");
@@ -192,6 +192,12 @@ static void build_impl(const flinng_params *p, const flinng_input *data, hipStre
         const uint64_t chunk = dense ? std::max<uint64_t>(1, (1ull << 29) / per_row) : (1ull << 20);
         for (uint64_t b0 = 0; b0 < N; b0 += chunk) {
             const uint64_t n = std::min(chunk, N - b0);
+            if (text) {
+                TextSource part = *text;
+                part.offsets += b0;
+                minhash_hash_text(*ix, part, n, codes.as<uint32_t>() + b0 * p->L, s);
+                continue;
+            }
             flinng_input part = slice(*data, *ix, b0, n);
             uint64_t ctr[2] = {0, 0};
             hash_batch(*ix, part, codes.as<uint32_t>() + b0 * p->L, s, dense ? ctr : nullptr);
@@ -225,9 +231,9 @@ int flinng_build_text(const flinng_params *p, const flinng_text *data, void *str
         hipStream_t s = static_cast<hipStream_t>(stream);
         const uint64_t nsym = text_symbols(*data);
         Scratch sc(nullptr, s);
-        flinng_input items{};
-        text_to_items(*data, p->family, nsym, s, sc, &items);
-        build_impl(p, &items, s, out);
+        const TextSource tx = text_source(*data, nsym, s, sc);
+        flinng_input sets{tx.symbols, tx.offsets, data->count, 1, 0};
+        build_impl(p, &sets, s, out, &tx);
     });
 }
 
@@ -326,7 +332,7 @@ static uint32_t *codes_scratch(const Index &ix, hipStream_t s, size_t bytes) {
 
 static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t k, uint32_t *ids,
                        uint32_t *scores, uint32_t out_on_device, uint32_t persistent,
-                       void *stream) {
+                       void *stream, const TextSource *text = nullptr) {
     require(idx != nullptr, "index is NULL");
     const Index &ix = *reinterpret_cast<const Index *>(idx);
     validate_input(q, ix.p.family, "queries");
@@ -339,7 +345,8 @@ static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t 
     std::shared_lock<std::shared_mutex> rl(ix.rw);  // one index version per call
     std::unique_lock<std::mutex> lock(ix.scratch_mu);
     uint32_t *codes = codes_scratch(ix, s, (size_t)nq * ix.p.L * 4);
-    hash_batch(ix, *q, codes, s, nullptr);
+    if (text) minhash_hash_text(ix, *text, nq, codes, s);
+    else hash_batch(ix, *q, codes, s, nullptr);
     DevBuf work(persistent ? 4 : 0, s);
     if (out_on_device) {
         query_launch(ix, codes, nq, k, ids, scores, persistent != 0, s, work.as<uint32_t>());
@@ -375,9 +382,9 @@ int flinng_query_text(const flinng_index *idx, const flinng_text *q, uint32_t k,
         hipStream_t s = static_cast<hipStream_t>(stream);
         const uint64_t nsym = text_symbols(*q);
         Scratch sc(nullptr, s);
-        flinng_input items{};
-        text_to_items(*q, ix.p.family, nsym, s, sc, &items);
-        query_impl(idx, &items, k, ids, scores, out_on_device, persistent, stream);
+        const TextSource tx = text_source(*q, nsym, s, sc);
+        const flinng_input sets{tx.symbols, tx.offsets, q->count, 1, 0};
+        query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx);
     });
 }
 

@@ -209,13 +209,19 @@ void srp_bound(const Index &ix, double *gamma, double *tau_abs);
 // Upper bound of the scratch srp_hash takes for n rows already on the device
 // (exact when the rows' device address xdev is given).
 size_t srp_scratch_bytes(const Index &ix, uint64_t n, const void *xdev = nullptr);
-void minhash_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev,
-                  hipStream_t s, double mean_hint = -1.0);
-// mean_hint: mean items per set of a device-resident set batch (<= 0: unknown).
+void minhash_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipStream_t s);
 // Device-resident inputs take no scratch beyond ws (MinHash takes none).
 void hash_batch(const Index &ix, const flinng_input &in, uint32_t *codes_dev,
-                hipStream_t s, uint64_t *counters_host, double mean_hint = -1.0,
-                Arena *ws = nullptr);
+                hipStream_t s, uint64_t *counters_host, Arena *ws = nullptr);
+// Symbol sequences on the device, read as n-gram sets (see flinng_text).
+struct TextSource {
+    const uint8_t *symbols;
+    const uint64_t *offsets;
+    uint64_t key;
+    uint32_t gram, radix;
+};
+void minhash_hash_text(const Index &ix, const TextSource &tx, uint64_t n, uint32_t *codes_dev,
+                       hipStream_t s);
 // Device bytes one served batch of nq queries (nitems set items) occupies:
 // staged input, codes, results and hash scratch, as the server carves them.
 uint64_t batch_device_bytes(const Index &ix, uint64_t nq, uint64_t nitems, uint32_t k,
@@ -223,13 +229,14 @@ uint64_t batch_device_bytes(const Index &ix, uint64_t nq, uint64_t nitems, uint3
 
 // N-gram text (text.hip).  validate_text: argument checks (FLINNG_EINVAL);
 // text_symbols: symbols the sequences span (reads two offsets back for a
-// device input); text_to_items: the item sets on the device (buffers from
-// sc), described by a device flinng_input of the family's item type.
+// device input); text_source: the sequences on the device (host text copied to
+// buffers from sc).
 void validate_text(const flinng_text *t, uint32_t family);
 uint64_t text_symbols(const flinng_text &t);
-void text_to_items(const flinng_text &t, uint32_t family, uint64_t nsym, hipStream_t s,
-                   Scratch &sc, flinng_input *out);
-// Device bytes text_to_items takes from an arena for n sequences of nsym symbols.
+TextSource text_source(const flinng_text &t, uint64_t nsym, hipStream_t s, Scratch &sc);
+// What the server's admission counts for the items of n sequences of nsym
+// symbols (its batches make them in registers; the bound is kept, so that a
+// memory budget admits what it did).
 inline size_t text_scratch_bytes(uint32_t family, uint64_t n, uint64_t nsym) {
     const size_t isz = family == FLINNG_MINHASH_U64 ? 8 : 4;
     return Arena::round((n + 1) * 8) + Arena::round((nsym ? nsym : 1) * isz);

@@ -72,6 +72,7 @@ __global__ __launch_bounds__(256) void transpose_codes_kernel(const uint32_t *__
 // of n costs about 4 R n instructions here, while a long run costs its
 // workgroup a pass over R*B bits.
 constexpr uint32_t RUN_TILE = 1024, RUN_SHORT = 32, RUN_LOAD = RUN_TILE + RUN_SHORT;
+constexpr uint32_t WORK_SAMPLE = 8;
 
 template <int RP>
 struct RowWords {
@@ -190,12 +191,17 @@ __global__ __launch_bounds__(256) void short_runs_kernel(
             const uint32_t j = tid + 256 * p;
             if (base + j < n) cnt[o + base + j] = aux[j];
         }
-        uint32_t sum = 0;  // list entries met by the runs' points as queries
+        // list entries met by the runs' points as queries: from one tile in
+        // WORK_SAMPLE (an estimate is all that is needed, and a counter that
+        // every tile added to would cost as much as the tiles)
+        if ((blockIdx.x + blockIdx.y) % WORK_SAMPLE == 0) {
+            uint32_t sum = 0;
 #pragma unroll
-        for (int p = 0; p < PER; ++p) sum += act[p] ? aux[st[p]] : 0u;
+            for (int p = 0; p < PER; ++p) sum += act[p] ? aux[st[p]] : 0u;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-        if (tid % 64 == 0 && sum) atomicAdd(work, (unsigned long long)sum);
+            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+            if (tid % 64 == 0 && sum) atomicAdd(work, (unsigned long long)sum * WORK_SAMPLE);
+        }
     } else {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {

@@ -96,9 +96,7 @@ extern "C" int flinng_query_noalloc(const flinng_index *idx, const flinng_input 
         Arena ws{device_scratch(), NOALLOC_SCRATCH_BYTES, 0};
         uint32_t *codes = static_cast<uint32_t *>(ws.take(nq * (size_t)ix.p.L * 4));
         uint32_t *work = static_cast<uint32_t *>(ws.take(4));
-        // device sets: no slice-count hint is read back, so the launch uses
-        // the default (the result does not depend on it)
-        hash_batch(ix, *q, codes, s, nullptr, -1.0, &ws);
+        hash_batch(ix, *q, codes, s, nullptr, &ws);
         query_launch(ix, codes, nq, k, ids, scores, persistent != 0, s, work);
         set_last_error("");
         return FLINNG_OK;

@@ -345,28 +345,15 @@ static void launch(Server &S, Lane &ln) {
     uint32_t *codes = reinterpret_cast<uint32_t *>(base + pl.codes);
     uint32_t *out = reinterpret_cast<uint32_t *>(base + pl.out);
     Arena ws{base + pl.hash, pl.total - pl.hash, 0};
-    double mean_hint = dense ? -1.0 : (double)ln.nitems / (double)nq;
-    if (ln.reqs[0]->text) {
-        // the staged symbols become n-gram items in the hash scratch
-        const Request &h = *ln.reqs[0];
-        flinng_text t{};
-        t.symbols = static_cast<const uint8_t *>(in.values);
-        t.offsets = in.offsets;
-        t.count = nq;
-        t.key = h.tkey;
-        t.gram = h.gram;
-        t.radix = h.radix;
-        t.on_device = 1;
-        Scratch sc(&ws, s);
-        text_to_items(t, ix.p.family, ln.nitems, s, sc, &in);
-        uint64_t nwin = 0;
-        for (const Request *r : ln.reqs) nwin += r->nwin;
-        mean_hint = (double)nwin / (double)nq;
-    }
     {
         // one index version per batch (an insert swaps arrays in between)
         std::shared_lock<std::shared_mutex> rl(ix.rw);
-        hash_batch(ix, in, codes, s, nullptr, mean_hint, &ws);
+        const Request &h = *ln.reqs[0];
+        if (h.text)  // the staged symbols and offsets, read as n-gram sets
+            minhash_hash_text(ix, TextSource{static_cast<const uint8_t *>(in.values), in.offsets, h.tkey,
+                                             h.gram, h.radix}, nq, codes, s);
+        else
+            hash_batch(ix, in, codes, s, nullptr, &ws);
         query_launch(ix, codes, nq, k, out, out + nq * k, S.cfg.persistent != 0, s,
                      reinterpret_cast<uint32_t *>(base + pl.work));
     }
