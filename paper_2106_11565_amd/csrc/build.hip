@@ -82,6 +82,114 @@ __global__ void member_slots_kernel(const uint64_t *__restrict__ pairs, uint64_t
     mem[b * mstride + (p - run)] = (uint32_t)pairs[p];
 }
 
+// The inverse of feistel.
+__device__ inline uint64_t feistel_inverse(uint64_t v, uint32_t half, const uint64_t *keys) {
+    const uint64_t mask = (1ull << half) - 1ull;
+    uint64_t hi = v >> half, lo = v & mask;
+#pragma unroll
+    for (int i = 3; i >= 0; --i) {
+        const uint64_t plo = hi;  // the round's input: (lo XOR F(plo), plo)
+        hi = lo ^ (splitmix_finalize(plo ^ keys[i]) & mask);
+        lo = plo;
+    }
+    return (hi << half) | lo;
+}
+
+// A group row (RP uint16) by vector loads and stores.
+template <int RP>
+struct GroupRow {
+    uint32_t w[(RP + 1) / 2];
+    __device__ void load(const uint16_t *p) {
+        if constexpr (RP == 1) w[0] = *p;
+        else if constexpr (RP == 2) w[0] = *reinterpret_cast<const uint32_t *>(p);
+        else if constexpr (RP == 4) *reinterpret_cast<uint2 *>(w) = *reinterpret_cast<const uint2 *>(p);
+        else
+#pragma unroll
+            for (int i = 0; i < RP / 8; ++i)
+                reinterpret_cast<uint4 *>(w)[i] = reinterpret_cast<const uint4 *>(p)[i];
+    }
+    __device__ void store(uint16_t *p) const {
+        if constexpr (RP == 1) *p = (uint16_t)w[0];
+        else if constexpr (RP == 2) *reinterpret_cast<uint32_t *>(p) = w[0];
+        else if constexpr (RP == 4) *reinterpret_cast<uint2 *>(p) = *reinterpret_cast<const uint2 *>(w);
+        else
+#pragma unroll
+            for (int i = 0; i < RP / 8; ++i)
+                reinterpret_cast<uint4 *>(p)[i] = reinterpret_cast<const uint4 *>(w)[i];
+    }
+};
+
+// One cell (r, b) per workgroup: its members are P_r^-1(b + j*B) for j below
+// its size, found by running the permutation backwards and sorted in LDS
+// (cap: a power of two at least mstride), with their group rows and filter
+// words.  A one-wavefront workgroup for cells of up to 512 members: no barrier
+// waits, and enough of them to fill the chip.  Replaces a stable sort of all
+// ids by group per repetition, and two gather passes: 5M points in 131,072
+// cells 6.5 -> 1.8 ms, 1M in 65,536 1.3 -> 0.2 ms.
+constexpr uint32_t CELL_CAP = 8192;
+template <int RP, int T>
+__global__ __launch_bounds__(T) void cells_kernel(uint64_t N, uint32_t R, uint32_t B, uint32_t half,
+                                                  GroupKeys gk, uint32_t mstride, uint32_t cap,
+                                                  const uint16_t *__restrict__ grp,
+                                                  uint32_t *__restrict__ mem, uint16_t *__restrict__ cmg,
+                                                  uint32_t *__restrict__ cfl,
+                                                  uint32_t *__restrict__ gsize) {
+    extern __shared__ uint32_t ids[];
+    const uint32_t b = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+    const uint32_t size = (uint32_t)(N / B + (b < N % B ? 1 : 0));
+    for (uint32_t j = tid; j < cap; j += T) {
+        uint32_t id = 0xFFFFFFFFu;
+        if (j < size) {
+            uint64_t x = feistel_inverse(b + (uint64_t)j * B, half, gk.k[r]);
+            while (x >= N) x = feistel_inverse(x, half, gk.k[r]);
+            id = (uint32_t)x;
+        }
+        ids[j] = id;
+    }
+    __syncthreads();
+    for (uint32_t run = 2; run <= cap; run <<= 1) {
+        for (uint32_t d = run >> 1; d; d >>= 1) {
+            for (uint32_t i = tid; i < cap / 2; i += T) {
+                const uint32_t lo = 2 * i - (i & (d - 1)), hi = lo + d;
+                const uint32_t p = ids[lo], q = ids[hi];
+                if ((p > q) == ((lo & run) == 0)) {
+                    ids[lo] = q;
+                    ids[hi] = p;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    const uint64_t slot0 = ((uint64_t)r * B + b) * mstride;
+    const uint32_t r1 = (r + 1) % R, r2 = (r + 2) % R;
+    for (uint32_t j = tid; j < mstride; j += T) {
+        const uint32_t x = ids[j];
+        GroupRow<RP> row{};
+        uint32_t f = 0;
+        if (x != 0xFFFFFFFFu) {
+            const uint16_t *g = grp + (uint64_t)x * RP;
+            row.load(g);
+            f = (uint32_t)g[r1] | ((uint32_t)g[r2] << 16);
+        }
+        mem[slot0 + j] = x;
+        row.store(cmg + (slot0 + j) * RP);
+        cfl[slot0 + j] = f;
+    }
+    if (tid == 0) gsize[(uint64_t)r * B + b] = size;
+}
+
+template <int RP>
+static void launch_cells(const Index &ix, uint32_t half, const GroupKeys &gk, uint32_t cap, hipStream_t s) {
+    const dim3 grid(ix.p.B, ix.p.R);
+    if (cap <= 512)
+        hipLaunchKernelGGL((cells_kernel<RP, 64>), grid, dim3(64), cap * 4, s, ix.N, ix.p.R, ix.p.B, half,
+                           gk, ix.mstride, cap, ix.grp, ix.mem, ix.cmg, ix.cfl, ix.gsize);
+    else
+        hipLaunchKernelGGL((cells_kernel<RP, 256>), grid, dim3(256), cap * 4, s, ix.N, ix.p.R, ix.p.B, half,
+                           gk, ix.mstride, cap, ix.grp, ix.mem, ix.cmg, ix.cfl, ix.gsize);
+    FL_CHECK_LAUNCH();
+}
+
 // cmg[slot][r] = group in repetition r of the member stored in mem[slot]
 // (zeros for the padding slots).
 __global__ void cell_groups_kernel(const uint32_t *__restrict__ mem, const uint16_t *__restrict__ grp,
@@ -131,9 +239,28 @@ void build_groups(Index &ix, hipStream_t s) {
     hipLaunchKernelGGL(groups_kernel, dim3(grid), dim3(256), 0, s, N, R, ix.Rp, B, nb / 2, gk,
                        ix.grp);
     FL_CHECK_LAUNCH();
-    // members of each cell, ascending id: stable sort of ids by group, then
-    // each group's run (at b*floor(N/B) + min(b, N mod B)) moves to its
-    // 16-byte aligned slot b*mstride; unused slot tails hold 0xFFFFFFFF
+    // cell sizes (Algorithm 1's balanced design), the host's copy
+    ix.gsize_host.assign((size_t)R * B, 0);
+    for (uint32_t r = 0; r < R; ++r)
+        for (uint32_t b = 0; b < B; ++b)
+            ix.gsize_host[(size_t)r * B + b] = (uint32_t)(N / B + (b < N % B ? 1 : 0));
+    ix.gmax = (uint32_t)((N + B - 1) / B);
+    // cells whose members fit a workgroup's LDS are made one per workgroup
+    uint32_t cap = 2;
+    while (cap < ix.mstride) cap <<= 1;
+    if (ix.mstride <= CELL_CAP) {
+        switch (ix.Rp) {
+            case 1: launch_cells<1>(ix, nb / 2, gk, cap, s); break;
+            case 2: launch_cells<2>(ix, nb / 2, gk, cap, s); break;
+            case 4: launch_cells<4>(ix, nb / 2, gk, cap, s); break;
+            case 8: launch_cells<8>(ix, nb / 2, gk, cap, s); break;
+            default: launch_cells<16>(ix, nb / 2, gk, cap, s); break;
+        }
+        return;
+    }
+    // larger cells: stable sort of ids by group, then each group's run (at
+    // b*floor(N/B) + min(b, N mod B)) moves to its 16-byte aligned slot
+    // b*mstride; unused slot tails hold 0xFFFFFFFF
     DevBuf keys(N * 4, s), pairs(N * 8, s), tmp(N * 8, s), ps(pair_sort_scratch_bytes(N, 1), s);
     int gbits = 1;
     while ((1u << gbits) < B) ++gbits;
@@ -152,12 +279,6 @@ void build_groups(Index &ix, hipStream_t s) {
                        ix.mem, ix.grp, nslots, ix.Rp, ix.cmg);
     FL_CHECK_LAUNCH();
     build_filter(ix, ix.mem, ix.grp, ix.mstride, ix.cfl, s);
-    // cell sizes (Algorithm 1's balanced design), on the device and the host
-    ix.gsize_host.assign((size_t)R * B, 0);
-    for (uint32_t r = 0; r < R; ++r)
-        for (uint32_t b = 0; b < B; ++b)
-            ix.gsize_host[(size_t)r * B + b] = (uint32_t)(N / B + (b < N % B ? 1 : 0));
-    ix.gmax = (uint32_t)((N + B - 1) / B);
     FL_HIP(hipMemcpyAsync(ix.gsize, ix.gsize_host.data(), (size_t)R * B * 4, hipMemcpyHostToDevice, s));
     FL_HIP(hipStreamSynchronize(s));  // the host vector is the copy's source
 }
