@@ -129,6 +129,9 @@ typedef struct flinng_index_info {
  *                 the library does not store the data (no vectors are kept).
  *  out    (host)  receives the new index; the library owns all its device
  *                 memory until flinng_index_free.
+ * Index arrays and build scratch come from a memory pool of the library, which
+ * keeps up to 4 GiB of freed memory mapped for the next build or insert while
+ * any index of the GPU lives, and gives everything back with the last one.
  * The call synchronizes `stream` before returning.
  */
 int flinng_build(const flinng_params *p, const flinng_input *data,
@@ -151,9 +154,11 @@ int flinng_build(const flinng_params *p, const flinng_input *data,
  * Device outputs: the call returns once the work is enqueued on `stream`.
  * Host outputs: the call synchronizes `stream`.  Queries only read the index,
  * so concurrent calls (from any threads, on any streams) are allowed, also
- * beside flinng_index_insert (each call sees one version of the index).  The batch's codes go to a device region the index keeps for
- * each stream it is queried on (up to 8 streams; allocated on first use,
- * grown synchronously for a larger batch, freed by flinng_index_free).
+ * beside flinng_index_insert (each call sees one version of the index).
+ * The batch's codes (and, where it is small, its other scratch) go to a device
+ * region the index keeps for each stream it is queried on (up to 8 streams;
+ * allocated on first use, grown synchronously for a larger batch, freed by
+ * flinng_index_free).
  */
 int flinng_query(const flinng_index *idx, const flinng_input *q, uint32_t k,
                  uint32_t *ids, uint32_t *scores, uint32_t out_on_device,

@@ -37,6 +37,80 @@ void DevBuf::release() {
 
 DevBuf::~DevBuf() { release(); }
 
+namespace {
+
+constexpr int POOL_DEVICES = 64;
+
+struct BuildPool {
+    std::mutex mu;
+    hipMemPool_t pool = nullptr;  // stays null where none can be made
+    bool tried = false;
+    int live = 0;                 // indexes of the device
+};
+
+BuildPool &build_pool(int dev) {
+    static BuildPool p[POOL_DEVICES];
+    return p[dev >= 0 && dev < POOL_DEVICES ? dev : 0];
+}
+
+hipMemPool_t pool_of(int dev) {
+    BuildPool &b = build_pool(dev);
+    std::lock_guard<std::mutex> lk(b.mu);
+    if (!b.tried) {
+        b.tried = true;
+        hipMemPoolProps props{};
+        props.allocType = hipMemAllocationTypePinned;
+        props.handleTypes = hipMemHandleTypeNone;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = dev;
+        uint64_t keep = POOL_KEEP;
+        if (hipMemPoolCreate(&b.pool, &props) != hipSuccess ||
+            hipMemPoolSetAttribute(b.pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+            b.pool = nullptr;
+            (void)hipGetLastError();
+        }
+    }
+    return b.pool;
+}
+
+}  // namespace
+
+void *pool_malloc(size_t bytes, hipStream_t s) {
+    int dev = 0;
+    FL_HIP(hipGetDevice(&dev));
+    hipMemPool_t pool = pool_of(dev);
+    void *p = nullptr;
+    hipError_t e = pool ? hipMallocFromPoolAsync(&p, bytes, pool, s) : hipMallocAsync(&p, bytes, s);
+    if (e == hipErrorOutOfMemory && pool) {  // what the pool keeps may be what is missing
+        (void)hipGetLastError();
+        (void)hipDeviceSynchronize();
+        (void)hipMemPoolTrimTo(pool, 0);
+        e = hipMallocFromPoolAsync(&p, bytes, pool, s);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        fail(e == hipErrorOutOfMemory ? FLINNG_ENOMEM : FLINNG_EDEVICE,
+             "device allocation of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
+    }
+    return p;
+}
+
+void pool_free(void *p) {
+    if (p) (void)hipFreeAsync(p, nullptr);
+}
+
+// An index joins or leaves its device's live ones; with the last the pool
+// gives everything back (the device is idle then).
+static void pool_live(int dev, int by) {
+    BuildPool &b = build_pool(dev);
+    std::lock_guard<std::mutex> lk(b.mu);
+    b.live += by;
+    if (b.live == 0 && b.pool) {
+        (void)hipStreamSynchronize(nullptr);  // the frees have happened
+        (void)hipMemPoolTrimTo(b.pool, 0);
+    }
+}
+
 template <class F>
 static int guard(F &&f) {
     try {
@@ -105,33 +179,24 @@ static flinng_input slice(const flinng_input &in, const Index &ix, uint64_t begi
 static void free_index(Index *ix) {
     if (!ix) return;
     (void)hipSetDevice(ix->device);
+    (void)hipDeviceSynchronize();  // queries may still be running on any stream
     for (auto &e : ix->scratch)
-        if (e.ptr) (void)hipFree(e.ptr);
-    if (ix->offsets) (void)hipFree(ix->offsets);
-    if (ix->cells) (void)hipFree(ix->cells);
-    if (ix->grp) (void)hipFree(ix->grp);
-    if (ix->mem) (void)hipFree(ix->mem);
-    if (ix->cmg) (void)hipFree(ix->cmg);
-    if (ix->cfl) (void)hipFree(ix->cfl);
-    if (ix->hyp) (void)hipFree(ix->hyp);
-    if (ix->hypnorm) (void)hipFree(ix->hypnorm);
-    if (ix->hypt) (void)hipFree(ix->hypt);
-    if (ix->gsize) (void)hipFree(ix->gsize);
+        if (e->ptr) (void)hipFree(e->ptr);
+    for (auto &r : ix->readbacks) {
+        (void)hipEventDestroy(r.ready);
+        (void)hipHostFree(r.host);
+    }
+    // (mem holds the member arrays, hyp the hyperplanes' arrays)
+    for (void *p : {static_cast<void *>(ix->offsets), ix->cells, static_cast<void *>(ix->grp),
+                    static_cast<void *>(ix->mem), static_cast<void *>(ix->hyp)})
+        pool_free(p);
+    if (ix->counted) pool_live(ix->device, -1);
     delete ix;
 }
 
 template <class T>
-static T *dmalloc(uint64_t n, uint64_t &acc) {
-    void *p = nullptr;
-    const size_t bytes = std::max<uint64_t>(n, 1) * sizeof(T);
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        fail(e == hipErrorOutOfMemory ? FLINNG_ENOMEM : FLINNG_EDEVICE,
-             "device allocation of " + std::to_string(bytes) + " bytes failed");
-    }
-    acc += bytes;
-    return static_cast<T *>(p);
+static T *dmalloc(uint64_t n, hipStream_t s) {
+    return static_cast<T *>(pool_malloc(std::max<uint64_t>(n, 1) * sizeof(T), s));
 }
 
 }  // namespace flinng
@@ -155,6 +220,8 @@ static void build_impl(const flinng_params *p, const flinng_input *data, hipStre
         ix->p = *p;
         ix->N = data->count;
         FL_HIP(hipGetDevice(&ix->device));
+        pool_live(ix->device, 1);
+        ix->counted = true;
         const bool dense = is_dense(p->family);
         ix->nbits = dense ? p->K : p->bucket_bits;
         if (dense) ix->p.bucket_bits = p->K;
@@ -164,25 +231,32 @@ static void build_impl(const flinng_params *p, const flinng_input *data, hipStre
         const uint32_t Bp = (p->B + 3) & ~3u;
         ix->cell_bytes = ((uint64_t)p->R * Bp <= 65536) ? 2 : 4;
         const uint64_t N = ix->N;
-        uint64_t bytes = 0;
         ix->N0 = N;
         ix->grp_cap = N;
-        ix->grp = dmalloc<uint16_t>(N * ix->Rp, bytes);
-        ix->gsize = dmalloc<uint32_t>((uint64_t)p->R * p->B, bytes);
+        ix->grp = dmalloc<uint16_t>(N * ix->Rp, s);
         const uint64_t gmax = (N + p->B - 1) / p->B;
         ix->mstride = (uint32_t)((gmax + 3) & ~3ull);
-        ix->mem = dmalloc<uint32_t>((uint64_t)p->R * p->B * ix->mstride, bytes);
-        ix->cmg = dmalloc<uint16_t>((uint64_t)p->R * p->B * ix->mstride * ix->Rp, bytes);
-        ix->cfl = dmalloc<uint32_t>((uint64_t)p->R * p->B * ix->mstride, bytes);
+        const MemberLayout ml((uint64_t)p->R * p->B, ix->mstride, ix->Rp);
+        char *mem = dmalloc<char>(ml.total, s);
+        ix->mem = reinterpret_cast<uint32_t *>(mem);
+        ix->cmg = reinterpret_cast<uint16_t *>(mem + ml.cmg);
+        ix->cfl = reinterpret_cast<uint32_t *>(mem + ml.cfl);
+        ix->gsize = reinterpret_cast<uint32_t *>(mem + ml.gsize);
         if (dense) {
-            ix->hyp = dmalloc<uint16_t>((uint64_t)p->L * p->K * ix->dpad, bytes);
-            ix->hypnorm = dmalloc<float>((uint64_t)p->L * p->K, bytes);
-            if (p->family == FLINNG_SRP_BF16)
-                ix->hypt = dmalloc<uint16_t>(((uint64_t)p->L * p->K + 15) / 16 * 16 * ix->dpad, bytes);
+            const uint64_t H = (uint64_t)p->L * p->K;
+            Pieces hp;
+            const size_t o_hyp = hp.add(H * ix->dpad * 2), o_norm = hp.add(H * 4);
+            const size_t o_tiled = hp.add(p->family == FLINNG_SRP_BF16 ? (H + 15) / 16 * 16 * ix->dpad * 2 : 0);
+            char *h = dmalloc<char>(hp.total, s);
+            ix->hyp = reinterpret_cast<uint16_t *>(h + o_hyp);
+            ix->hypnorm = reinterpret_cast<float *>(h + o_norm);
+            if (p->family == FLINNG_SRP_BF16) ix->hypt = reinterpret_cast<uint16_t *>(h + o_tiled);
             srp_make_hyperplanes(*ix, s);
         }
         // hash all points (in chunks to bound scratch memory)
-        DevBuf codes(N * p->L * 4, s);
+        DevBuf codes = DevBuf::pooled(N * p->L * 4, s), ctrs = DevBuf::pooled(dense ? 16 : 0, s);
+        unsigned long long *ctr = dense ? ctrs.as<unsigned long long>() : nullptr;
+        if (ctr) zero_counters(ctr, s);
         // dense chunks bound the SRP scratch (a device copy of host rows,
         // operand planes): 512 MB of bf16 rows (the fused kernel takes them
         // in place, and larger batches fill more rounds of workgroups), or
@@ -199,14 +273,15 @@ static void build_impl(const flinng_params *p, const flinng_input *data, hipStre
                 continue;
             }
             flinng_input part = slice(*data, *ix, b0, n);
-            uint64_t ctr[2] = {0, 0};
-            hash_batch(*ix, part, codes.as<uint32_t>() + b0 * p->L, s, dense ? ctr : nullptr);
-            ix->srp_rechecked += ctr[0];
-            ix->srp_exact += ctr[1];
+            hash_batch(*ix, part, codes.as<uint32_t>() + b0 * p->L, s, ctr);
         }
         build_groups(*ix, s);
         build_lists(*ix, codes.as<uint32_t>(), s);
+        uint64_t counted[2] = {0, 0};
+        if (ctr) FL_HIP(hipMemcpyAsync(counted, ctr, 16, hipMemcpyDeviceToHost, s));
         FL_HIP(hipStreamSynchronize(s));
+        ix->srp_rechecked = counted[0];
+        ix->srp_exact = counted[1];
         ix->device_bytes = index_device_bytes(*ix);
     } catch (...) {
         free_index(ix);
@@ -251,24 +326,27 @@ int flinng_index_insert(flinng_index *idx, const flinng_input *data, void *strea
         std::lock_guard<std::mutex> one(ix.insert_mu);
         require(ix.N + n <= 0xFFFFFFFEull, "at most 2^32-2 points");
         const bool dense = is_dense(ix.p.family);
-        DevBuf codes(n * ix.p.L * 4, s);
+        DevBuf codes = DevBuf::pooled(n * ix.p.L * 4, s), ctrs = DevBuf::pooled(dense ? 16 : 0, s);
+        unsigned long long *ctr = dense ? ctrs.as<unsigned long long>() : nullptr;
+        if (ctr) zero_counters(ctr, s);
         const uint64_t per_row =
             (uint64_t)ix.dpad * (ix.p.family == FLINNG_SRP_BF16 ? 2 : 16);  // as in the build
         const uint64_t chunk = dense ? std::max<uint64_t>(1, (1ull << 29) / per_row)
                                      : (1ull << 20);
-        uint64_t rechecked = 0, exact = 0;
         for (uint64_t b0 = 0; b0 < n; b0 += chunk) {
             const uint64_t m = std::min(chunk, n - b0);
             flinng_input part = slice(*data, ix, b0, m);
-            uint64_t ctr[2] = {0, 0};
-            hash_batch(ix, part, codes.as<uint32_t>() + b0 * ix.p.L, s, dense ? ctr : nullptr);
-            rechecked += ctr[0];
-            exact += ctr[1];
+            hash_batch(ix, part, codes.as<uint32_t>() + b0 * ix.p.L, s, ctr);
         }
         insert_points(ix, codes.as<uint32_t>(), n, s);
+        uint64_t counted[2] = {0, 0};
+        if (ctr) {
+            FL_HIP(hipMemcpyAsync(counted, ctr, 16, hipMemcpyDeviceToHost, s));
+            FL_HIP(hipStreamSynchronize(s));
+        }
         std::unique_lock<std::shared_mutex> lk(ix.rw);
-        ix.srp_rechecked += rechecked;
-        ix.srp_exact += exact;
+        ix.srp_rechecked += counted[0];
+        ix.srp_exact += counted[1];
     });
 }
 
@@ -294,41 +372,105 @@ int flinng_index_get_info(const flinng_index *idx, flinng_index_info *info) {
     });
 }
 
-// The index's codes region for stream s, at least `bytes` long (see
-// Index::scratch), with ix.scratch_mu held by the caller until the work that
-// uses it is queued (two threads queueing on one stream must not interleave
-// their hash and query launches).  At most 8 streams are remembered; the
-// oldest is evicted.
-static uint32_t *codes_scratch(const Index &ix, hipStream_t s, size_t bytes) {
-    Index::StreamScratch *slot = nullptr;
-    for (auto &e : ix.scratch)
-        if (e.stream == s) slot = &e;
-    if (slot && slot->cap >= bytes) return static_cast<uint32_t *>(slot->ptr);
-    if (!slot) {
-        if (ix.scratch.size() >= 8) {
-            if (ix.scratch.front().ptr) (void)hipFree(ix.scratch.front().ptr);
-            ix.scratch.erase(ix.scratch.begin());
+}  // extern "C"
+
+// The index's region for stream s, at least `bytes` long, and its lock (see
+// Index::StreamScratch).  At most 8 streams are remembered; the oldest that no
+// call holds is evicted.
+using ScratchLock = std::unique_lock<std::mutex>;
+static std::shared_ptr<Index::StreamScratch> lock_scratch(const Index &ix, hipStream_t s, size_t bytes,
+                                                          ScratchLock &lock) {
+    std::shared_ptr<Index::StreamScratch> e;
+    for (;;) {
+        {
+            std::lock_guard<std::mutex> lk(ix.scratch_mu);
+            e.reset();
+            for (auto &x : ix.scratch)
+                if (x->stream == s) e = x;
+            if (!e) {
+                for (auto it = ix.scratch.begin(); ix.scratch.size() >= 8 && it != ix.scratch.end();) {
+                    ScratchLock l((*it)->mu, std::try_to_lock);
+                    if (!l) {
+                        ++it;
+                        continue;
+                    }
+                    if ((*it)->ptr) (void)hipFree((*it)->ptr);
+                    (*it)->ptr = nullptr;
+                    (*it)->evicted = true;
+                    l.unlock();
+                    it = ix.scratch.erase(it);
+                }
+                e = std::make_shared<Index::StreamScratch>();
+                e->stream = s;
+                ix.scratch.push_back(e);
+            }
         }
-        ix.scratch.push_back({s, nullptr, 0});
-        slot = &ix.scratch.back();
+        lock = ScratchLock(e->mu);
+        if (!e->evicted) break;
+        lock.unlock();
     }
-    if (slot->ptr) (void)hipFree(slot->ptr);  // waits for the work using it
-    slot->ptr = nullptr;
-    slot->cap = 0;
+    if (e->cap >= bytes) return e;
+    if (e->ptr) (void)hipFree(e->ptr);  // waits for the work using it
+    e->ptr = nullptr;
+    e->cap = 0;
     const size_t cap = std::max<size_t>(bytes, 64 * 1024);
     void *p = nullptr;
-    const hipError_t e = hipMalloc(&p, cap);
-    if (e != hipSuccess) {
+    const hipError_t err = hipMalloc(&p, cap);
+    if (err != hipSuccess) {
         (void)hipGetLastError();
-        fail(e == hipErrorOutOfMemory ? FLINNG_ENOMEM : FLINNG_EDEVICE,
+        fail(err == hipErrorOutOfMemory ? FLINNG_ENOMEM : FLINNG_EDEVICE,
              "device allocation of " + std::to_string(cap) + " bytes failed");
     }
-    slot->ptr = p;
-    slot->cap = cap;
-    return static_cast<uint32_t *>(p);
+    e->ptr = p;
+    e->cap = cap;
+    return e;
 }
 
-}  // extern "C"
+namespace {
+
+// A Readback of the index for one call; waited for before it is given back.
+struct ReadbackLease {
+    const Index &ix;
+    Index::Readback r{};
+    bool pending = false;
+    explicit ReadbackLease(const Index &i) : ix(i) {
+        {
+            std::lock_guard<std::mutex> lk(ix.readback_mu);
+            if (!ix.readbacks.empty()) {
+                r = ix.readbacks.back();
+                ix.readbacks.pop_back();
+                return;
+            }
+        }
+        void *p = nullptr;
+        FL_HIP(hipHostMalloc(&p, 16, hipHostMallocDefault));
+        r.host = static_cast<uint64_t *>(p);
+        if (hipEventCreateWithFlags(&r.ready, hipEventDisableTiming) != hipSuccess) {
+            (void)hipHostFree(p);
+            fail(FLINNG_EDEVICE, "event creation failed");
+        }
+    }
+    void wait() {
+        if (!pending) return;
+        pending = false;
+        FL_HIP(hipEventSynchronize(r.ready));
+    }
+    ~ReadbackLease() {
+        if (pending) (void)hipEventSynchronize(r.ready);
+        try {
+            std::lock_guard<std::mutex> lk(ix.readback_mu);
+            ix.readbacks.push_back(r);
+        } catch (...) {  // no room to remember it: not kept
+            (void)hipEventDestroy(r.ready);
+            (void)hipHostFree(r.host);
+        }
+    }
+};
+
+}  // namespace
+
+// Scratch of a batch that is kept in its stream's region rather than allocated.
+constexpr size_t SMALL_SCRATCH = (size_t)1 << 20;
 
 static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t k, uint32_t *ids,
                        uint32_t *scores, uint32_t out_on_device, uint32_t persistent,
@@ -343,23 +485,58 @@ static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t 
     FL_HIP(hipSetDevice(ix.device));
     hipStream_t s = static_cast<hipStream_t>(stream);
     std::shared_lock<std::shared_mutex> rl(ix.rw);  // one index version per call
-    std::unique_lock<std::mutex> lock(ix.scratch_mu);
-    uint32_t *codes = codes_scratch(ix, s, (size_t)nq * ix.p.L * 4);
-    if (text) minhash_hash_text(ix, *text, nq, codes, s);
-    else hash_batch(ix, *q, codes, s, nullptr);
-    DevBuf work(persistent ? 4 : 0, s);
+    // the region of this stream holds the codes and, for a batch whose other
+    // scratch is small, that too (a copy of host rows, the SRP stage's planes,
+    // results on their way to the host): a lookup of one row then allocates
+    // nothing
+    const bool dense = is_dense(ix.p.family), host_rows = dense && !q->on_device;
+    const size_t row_bytes = (size_t)ix.p.dim * (ix.p.family == FLINNG_SRP_F32 ? 4 : 2);
+    const size_t code_bytes = Arena::round((size_t)nq * ix.p.L * 4) + Arena::round(4);
+    const size_t in_bytes = host_rows ? Arena::round(nq * row_bytes) : 0;
+    const size_t res_bytes = out_on_device ? 0 : Arena::round((size_t)nq * k * 4) * (scores ? 2 : 1);
+    const size_t srp_bytes = dense ? srp_scratch_bytes(ix, nq, host_rows ? nullptr : q->values) : 0;
+    const bool all = in_bytes + res_bytes + srp_bytes <= SMALL_SCRATCH;
+    Arena a{nullptr, code_bytes + (all ? in_bytes + res_bytes + srp_bytes : 0), 0};
+    ScratchLock lock;
+    const auto region = lock_scratch(ix, s, a.cap, lock);
+    a.base = static_cast<char *>(region->ptr);
+    uint32_t *codes = static_cast<uint32_t *>(a.take((size_t)nq * ix.p.L * 4));
+    uint32_t *work = static_cast<uint32_t *>(a.take(4));
+    if (text) {
+        minhash_hash_text(ix, *text, nq, codes, s);
+    } else if (all && dense) {
+        flinng_input in = *q;
+        if (host_rows) {
+            in.values = a.take(nq * row_bytes);
+            in.on_device = 1;
+            FL_HIP(hipMemcpyAsync(const_cast<void *>(in.values), q->values, nq * row_bytes,
+                                  hipMemcpyHostToDevice, s));
+        }
+        hash_batch(ix, in, codes, s, nullptr, &a);
+    } else {
+        hash_batch(ix, *q, codes, s, nullptr);
+    }
     if (out_on_device) {
-        query_launch(ix, codes, nq, k, ids, scores, persistent != 0, s, work.as<uint32_t>());
+        query_launch(ix, codes, nq, k, ids, scores, persistent != 0, s, work);
         lock.unlock();
         rl.unlock();
     } else {
-        DevBuf dids(nq * k * 4, s), dsc(scores ? nq * k * 4 : 0, s);
-        query_launch(ix, codes, nq, k, dids.as<uint32_t>(), scores ? dsc.as<uint32_t>() : nullptr,
-                     persistent != 0, s, work.as<uint32_t>());
-        lock.unlock();
+        DevBuf own;
+        uint32_t *dids, *dsc = nullptr;
+        if (all) {
+            dids = static_cast<uint32_t *>(a.take(nq * k * 4));
+            if (scores) dsc = static_cast<uint32_t *>(a.take(nq * k * 4));
+        } else {
+            own = DevBuf(nq * k * 8, s);
+            dids = own.as<uint32_t>();
+            if (scores) dsc = dids + nq * k;
+        }
+        query_launch(ix, codes, nq, k, dids, dsc, persistent != 0, s, work);
         rl.unlock();
-        FL_HIP(hipMemcpyAsync(ids, dids.ptr, nq * k * 4, hipMemcpyDeviceToHost, s));
-        if (scores) FL_HIP(hipMemcpyAsync(scores, dsc.ptr, nq * k * 4, hipMemcpyDeviceToHost, s));
+        // results in the region: it stays this call's until they are copied
+        if (!all) lock.unlock();
+        FL_HIP(hipMemcpyAsync(ids, dids, nq * k * 4, hipMemcpyDeviceToHost, s));
+        if (scores) FL_HIP(hipMemcpyAsync(scores, dsc, nq * k * 4, hipMemcpyDeviceToHost, s));
         FL_HIP(hipStreamSynchronize(s));
     }
 }
@@ -380,11 +557,25 @@ int flinng_query_text(const flinng_index *idx, const flinng_text *q, uint32_t k,
         if (q->count == 0) return;
         FL_HIP(hipSetDevice(ix.device));
         hipStream_t s = static_cast<hipStream_t>(stream);
-        const uint64_t nsym = text_symbols(*q);
         Scratch sc(nullptr, s);
-        const TextSource tx = text_source(*q, nsym, s, sc);
+        if (!q->on_device) {
+            const TextSource tx = text_source(*q, text_symbols(*q), s, sc);
+            const flinng_input sets{tx.symbols, tx.offsets, q->count, 1, 0};
+            query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx);
+            return;
+        }
+        // the first and last offset are read back while the batch is hashed
+        // (which reads no symbol where they decrease), and refused after
+        ReadbackLease rb(ix);
+        FL_HIP(hipMemcpyAsync(rb.r.host, q->offsets, 8, hipMemcpyDeviceToHost, s));
+        FL_HIP(hipMemcpyAsync(rb.r.host + 1, q->offsets + q->count, 8, hipMemcpyDeviceToHost, s));
+        FL_HIP(hipEventRecord(rb.r.ready, s));
+        rb.pending = true;
+        const TextSource tx = text_source(*q, 0, s, sc);
         const flinng_input sets{tx.symbols, tx.offsets, q->count, 1, 0};
         query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx);
+        rb.wait();
+        require(rb.r.host[1] >= rb.r.host[0], "text offsets must be nondecreasing");
     });
 }
 

@@ -261,7 +261,8 @@ void build_groups(Index &ix, hipStream_t s) {
     // larger cells: stable sort of ids by group, then each group's run (at
     // b*floor(N/B) + min(b, N mod B)) moves to its 16-byte aligned slot
     // b*mstride; unused slot tails hold 0xFFFFFFFF
-    DevBuf keys(N * 4, s), pairs(N * 8, s), tmp(N * 8, s), ps(pair_sort_scratch_bytes(N, 1), s);
+    DevBuf keys = DevBuf::pooled(N * 4, s), pairs = DevBuf::pooled(N * 8, s),
+           tmp = DevBuf::pooled(N * 8, s), ps = DevBuf::pooled(pair_sort_scratch_bytes(N, 1), s);
     int gbits = 1;
     while ((1u << gbits) < B) ++gbits;
     FL_HIP(hipMemsetAsync(ix.mem, 0xFF, (size_t)R * B * ix.mstride * 4, s));
@@ -371,10 +372,9 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
     if (x0 + n > 0xFFFFFFFEull) fail(FLINNG_EINVAL, "at most 2^32-2 points");
     const uint32_t R = ix.p.R, B = ix.p.B, Rp = ix.Rp;
     const uint64_t ncells = (uint64_t)R * B;
-    auto dfree = [](void *p) { if (p) (void)hipFree(p); };
     // arrays of the new version (freed on failure)
-    uint16_t *grp1 = nullptr, *cmg1 = nullptr;
-    uint32_t *mem1 = nullptr, *gsize1 = nullptr, *cfl1 = nullptr;
+    uint16_t *grp1 = nullptr;
+    char *slab = nullptr;
     Lists lists;
     try {
         // 1. group rows of the arrivals (grp is not read by queries; a larger
@@ -382,7 +382,7 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         uint16_t *grp = ix.grp;
         if (x0 + n > ix.grp_cap) {
             const uint64_t cap = std::max<uint64_t>(x0 + n, ix.grp_cap + ix.grp_cap / 2);
-            FL_HIP(hipMalloc(&grp1, cap * Rp * 2));
+            grp1 = static_cast<uint16_t *>(pool_malloc(cap * Rp * 2, s));
             FL_HIP(hipMemcpyAsync(grp1, ix.grp, x0 * Rp * 2, hipMemcpyDeviceToDevice, s));
             grp = grp1;
         }
@@ -395,24 +395,32 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         // 2. arrivals sorted by group, per repetition; new cell sizes
         int gbits = 1;
         while ((1u << gbits) < B) ++gbits;
-        DevBuf skeys(n * R * 4, s), pairs(n * R * 8, s), tmp(n * R * 8, s),
-            ps(pair_sort_scratch_bytes(n, R), s);
-        DevBuf starts(ncells * 4, s), ends(ncells * 4, s), cnt(ncells * 4, s);
-        FL_HIP(hipMemsetAsync(starts.ptr, 0, ncells * 4, s));
-        FL_HIP(hipMemsetAsync(ends.ptr, 0, ncells * 4, s));
+        Pieces pc;
+        const size_t o_keys = pc.add(n * R * 4), o_pairs = pc.add(n * R * 8), o_tmp = pc.add(n * R * 8),
+                     o_ps = pc.add(pair_sort_scratch_bytes(n, R)), o_starts = pc.add(ncells * 4),
+                     o_ends = pc.add(ncells * 4), o_cnt = pc.add(ncells * 4);
+        DevBuf ws = DevBuf::pooled(pc.total, s);
+        char *w = ws.as<char>();
+        uint32_t *skeys = reinterpret_cast<uint32_t *>(w + o_keys);
+        uint64_t *pairs = reinterpret_cast<uint64_t *>(w + o_pairs);
+        uint32_t *starts = reinterpret_cast<uint32_t *>(w + o_starts);
+        uint32_t *ends = reinterpret_cast<uint32_t *>(w + o_ends);
+        uint32_t *cnt = reinterpret_cast<uint32_t *>(w + o_cnt);
+        FL_HIP(hipMemsetAsync(starts, 0, ncells * 4, s));
+        FL_HIP(hipMemsetAsync(ends, 0, ncells * 4, s));
         hipLaunchKernelGGL(member_keys_kernel, dim3(gn, R), dim3(256), 0, s, grp, x0, n, Rp, 0u,
-                           skeys.as<uint32_t>());
+                           skeys);
         FL_CHECK_LAUNCH();
-        pair_sort(skeys.as<uint32_t>(), n, R, gbits, pairs.as<uint64_t>(), tmp.as<uint64_t>(), ps.ptr, s);
-        hipLaunchKernelGGL(run_bounds_kernel, dim3(gn, R), dim3(256), 0, s, pairs.as<uint64_t>(), n, B,
-                           starts.as<uint32_t>(), ends.as<uint32_t>());
+        pair_sort(skeys, n, R, gbits, pairs, reinterpret_cast<uint64_t *>(w + o_tmp), w + o_ps, s);
+        hipLaunchKernelGGL(run_bounds_kernel, dim3(gn, R), dim3(256), 0, s, pairs, n, B,
+                           starts, ends);
         FL_CHECK_LAUNCH();
         hipLaunchKernelGGL(run_counts_kernel, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0, s,
-                           starts.as<uint32_t>(), ends.as<uint32_t>(), (uint32_t)ncells,
-                           cnt.as<uint32_t>());
+                           starts, ends, (uint32_t)ncells,
+                           cnt);
         FL_CHECK_LAUNCH();
         std::vector<uint32_t> add(ncells);
-        FL_HIP(hipMemcpyAsync(add.data(), cnt.ptr, ncells * 4, hipMemcpyDeviceToHost, s));
+        FL_HIP(hipMemcpyAsync(add.data(), cnt, ncells * 4, hipMemcpyDeviceToHost, s));
         FL_HIP(hipStreamSynchronize(s));
         std::vector<uint32_t> gs1(ix.gsize_host);
         uint32_t gmax1 = 0;
@@ -424,8 +432,12 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         //    a cell outgrows the old one, then the arrivals appended
         uint32_t ms1 = ix.mstride;
         if (gmax1 > ms1) ms1 = (uint32_t)((std::max<uint64_t>(gmax1, ms1 + ms1 / 2) + 3) & ~3ull);
-        FL_HIP(hipMalloc(&mem1, ncells * ms1 * 4));
-        FL_HIP(hipMalloc(&cmg1, ncells * ms1 * Rp * 2));
+        const MemberLayout ml(ncells, ms1, Rp);
+        slab = static_cast<char *>(pool_malloc(ml.total, s));
+        uint32_t *mem1 = reinterpret_cast<uint32_t *>(slab);
+        uint16_t *cmg1 = reinterpret_cast<uint16_t *>(slab + ml.cmg);
+        uint32_t *cfl1 = reinterpret_cast<uint32_t *>(slab + ml.cfl);
+        uint32_t *gsize1 = reinterpret_cast<uint32_t *>(slab + ml.gsize);
         if (ms1 == ix.mstride) {
             FL_HIP(hipMemcpyAsync(mem1, ix.mem, ncells * ms1 * 4, hipMemcpyDeviceToDevice, s));
             FL_HIP(hipMemcpyAsync(cmg1, ix.cmg, ncells * ms1 * Rp * 2, hipMemcpyDeviceToDevice, s));
@@ -437,14 +449,12 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
                                ix.mem, ix.cmg, ncells, ix.mstride, ms1, Rp, mem1, cmg1);
             FL_CHECK_LAUNCH();
         }
-        hipLaunchKernelGGL(place_members_kernel, dim3(gn, R), dim3(256), 0, s, pairs.as<uint64_t>(), n,
-                           x0, starts.as<uint32_t>(), ix.gsize, B, ms1, grp, Rp, mem1, cmg1);
+        hipLaunchKernelGGL(place_members_kernel, dim3(gn, R), dim3(256), 0, s, pairs, n,
+                           x0, starts, ix.gsize, B, ms1, grp, Rp, mem1, cmg1);
         FL_CHECK_LAUNCH();
-        FL_HIP(hipMalloc(&cfl1, ncells * ms1 * 4));
         build_filter(ix, mem1, grp, ms1, cfl1, s);
-        FL_HIP(hipMalloc(&gsize1, ncells * 4));
         hipLaunchKernelGGL(add_u32_kernel, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0, s,
-                           ix.gsize, cnt.as<uint32_t>(), ncells, gsize1);
+                           ix.gsize, cnt, ncells, gsize1);
         FL_CHECK_LAUNCH();
         // 4. reverse index: the arrivals' cells merged into the old lists
         lists = merge_lists(ix, codes, grp + x0 * Rp, n, s);
@@ -452,8 +462,7 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         // 5. swap the new version in while no query is being enqueued, and
         //    free the old one once the device has finished all work using it
         std::unique_lock<std::shared_mutex> lk(ix.rw);
-        void *old[7] = {ix.offsets, ix.cells, ix.mem, ix.cmg, ix.cfl, ix.gsize,
-                        grp1 ? ix.grp : nullptr};
+        void *old[4] = {ix.offsets, ix.cells, ix.mem, grp1 ? ix.grp : nullptr};
         ix.offsets = lists.offsets;
         ix.cells = lists.cells;
         // (kept as it was, scaled: it only chooses between query kernels)
@@ -473,19 +482,14 @@ void insert_points(Index &ix, const uint32_t *codes, uint64_t n, hipStream_t s) 
         ix.N = x0 + n;
         ix.device_bytes = index_device_bytes(ix);
         lists = Lists();
-        mem1 = nullptr;
-        cmg1 = nullptr;
-        cfl1 = nullptr;
-        gsize1 = nullptr;
+        slab = nullptr;
         grp1 = nullptr;
         FL_HIP(hipDeviceSynchronize());
-        for (void *p : old) dfree(p);
+        for (void *p : old) pool_free(p);
     } catch (...) {
-        dfree(grp1);
-        dfree(mem1);
-        dfree(cmg1);
-        dfree(cfl1);
-        dfree(gsize1);
+        (void)hipDeviceSynchronize();
+        pool_free(grp1);
+        pool_free(slab);
         free_lists(lists);
         throw;
     }

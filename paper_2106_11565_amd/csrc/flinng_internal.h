@@ -3,9 +3,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
 #include <mutex>
 #include <shared_mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/flinng.h"
@@ -107,17 +109,30 @@ struct Index {
     std::vector<uint32_t> gsize_host;     // host copy of gsize
     mutable std::shared_mutex rw;         // query enqueue (shared) / insert swap
     std::mutex insert_mu;                 // one insert at a time
-    // Device scratch for the codes of one query batch, one region per
-    // stream the index is queried on: work on one stream runs in order, so
-    // a region is reused without waiting.  Grown (and evicted) with a
-    // synchronous free; released with the index.
+    // Device scratch of one query batch (its codes above all), one region per
+    // stream the index is queried on: work on one stream runs in order, so a
+    // region is reused without waiting.  Its lock is held while a call queues
+    // the work that uses it (two threads queueing on one stream must not
+    // interleave) and, where its results lie in it, until they are copied out.
+    // Grown (and evicted) with a synchronous free; released with the index.
     struct StreamScratch {
-        hipStream_t stream;
-        void *ptr;
-        size_t cap;
+        hipStream_t stream = nullptr;
+        void *ptr = nullptr;
+        size_t cap = 0;
+        bool evicted = false;
+        std::mutex mu;
     };
     mutable std::mutex scratch_mu;
-    mutable std::vector<StreamScratch> scratch;
+    mutable std::vector<std::shared_ptr<StreamScratch>> scratch;
+    // Pinned words that a text query reads its first and last offset into,
+    // with the event that says they are there: one per call in flight.
+    struct Readback {
+        uint64_t *host;
+        hipEvent_t ready;
+    };
+    mutable std::mutex readback_mu;
+    mutable std::vector<Readback> readbacks;  // the free ones
+    bool counted = false;                 // among its device's live indexes
 };
 
 inline uint64_t nbuckets(const Index &ix) { return 1ull << ix.nbits; }
@@ -139,12 +154,43 @@ inline uint64_t index_device_bytes(const Index &ix) {
     return b;
 }
 
+// The member arrays of an index (mem, cmg, cfl, gsize) lie in one allocation,
+// mem first, at 256-byte aligned offsets: an insert replaces them together.
+struct MemberLayout {
+    size_t cmg, cfl, gsize, total;
+    MemberLayout(uint64_t ncells, uint64_t mstride, uint32_t Rp) {
+        auto round = [](size_t b) { return (b + 255) & ~(size_t)255; };
+        cmg = round(ncells * mstride * 4);
+        cfl = cmg + round(ncells * mstride * Rp * 2);
+        gsize = cfl + round(ncells * mstride * 4);
+        total = gsize + round(ncells * 4);
+    }
+};
+
+// Device memory of builds and inserts: the arrays of indexes and the scratch
+// that makes them, from a stream-ordered pool of the library's own (one per
+// GPU).  Mapping and unmapping device memory costs milliseconds per call at
+// times (a hipFree 1.6 ms on average, up to 15 ms, in runs where a stream of
+// inserts took 155 ms instead of 40), so up to POOL_KEEP bytes that are not in
+// use stay mapped for the next build or insert; with the last index of a GPU
+// everything is given back.  pool_free: the caller knows that the device no
+// longer uses the memory.
+constexpr uint64_t POOL_KEEP = 4ull << 30;
+void *pool_malloc(size_t bytes, hipStream_t s);
+void pool_free(void *p);
+
 // Device scratch allocated on a stream (stream-ordered allocator).
 struct DevBuf {
     void *ptr = nullptr;
     hipStream_t stream = nullptr;
     DevBuf() = default;
     DevBuf(size_t bytes, hipStream_t s);
+    static DevBuf pooled(size_t bytes, hipStream_t s) {
+        DevBuf b;
+        b.stream = s;
+        if (bytes) b.ptr = pool_malloc(bytes, s);
+        return b;
+    }
     ~DevBuf();
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
@@ -178,6 +224,16 @@ struct Arena {
     }
 };
 
+// Pieces of one allocation: sizes added first, pointers once it exists.
+struct Pieces {
+    size_t total = 0;
+    size_t add(size_t bytes) {
+        const size_t at = total;
+        total += Arena::round(bytes);
+        return at;
+    }
+};
+
 // Scratch of one call: carved from an arena when one is given, otherwise
 // allocated on the stream and freed on it when the Scratch goes away.
 struct Scratch {
@@ -196,12 +252,12 @@ struct Scratch {
 // ---------------------------------------------------------------------------
 // Hashing (hash_srp.hip, hash_minhash.hip).  All write codes[n][L] uint32.
 void srp_make_hyperplanes(Index &ix, hipStream_t s);
-// Returns (rechecked, exact) counts when counters != nullptr (synchronizes).
-// Scratch comes from ws when given (srp_scratch_bytes bounds what it takes).
+// ctr (device, optional): the rechecked and exactly decided projections are
+// added to its two counts.  Scratch comes from ws when given (srp_scratch_bytes bounds what it takes).
 // proj_dev (optional, device, n*L*K fp32): receives the MFMA projections
 // before any recheck.
 void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev,
-              hipStream_t s, uint64_t *counters_host, Arena *ws = nullptr,
+              hipStream_t s, unsigned long long *ctr, Arena *ws = nullptr,
               float *proj_dev = nullptr);
 // The error bound the MFMA stage uses for a trusted sign: |v32 - v| <=
 // gamma * |x|_2 * |w|_2 + tau_abs (rounding of the norms included).
@@ -212,7 +268,8 @@ size_t srp_scratch_bytes(const Index &ix, uint64_t n, const void *xdev = nullptr
 void minhash_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipStream_t s);
 // Device-resident inputs take no scratch beyond ws (MinHash takes none).
 void hash_batch(const Index &ix, const flinng_input &in, uint32_t *codes_dev,
-                hipStream_t s, uint64_t *counters_host, Arena *ws = nullptr);
+                hipStream_t s, unsigned long long *ctr, Arena *ws = nullptr);
+void zero_counters(unsigned long long *ctr, hipStream_t s);  // the two of srp_hash
 // Symbol sequences on the device, read as n-gram sets (see flinng_text).
 struct TextSource {
     const uint8_t *symbols;
@@ -298,7 +355,6 @@ void query_launch(const Index &ix, const uint32_t *codes_dev, uint64_t nq,
                   unsigned long long *stats = nullptr);
 void counts_launch(const Index &ix, const uint32_t *codes_dev, uint64_t nq,
                    uint8_t *counts_dev, hipStream_t s);
-size_t query_lds_bytes(const Index &ix, uint32_t k);
 uint32_t query_max_k();
 
 // Scratch bytes flinng_query_noalloc carves for nq queries (noalloc.hip).

@@ -119,7 +119,11 @@ __global__ __launch_bounds__(256) void minhash_kernel(const ItemT *__restrict__ 
     const uint64_t *off = TEXT ? tx.offsets : offsets;
     const uint64_t beg = off[set], end = off[set + 1];
     uint64_t n = end > beg ? end - beg : 0;
-    if (TEXT) n = n >= tx.gram ? n - tx.gram + 1 : 0;
+    if (TEXT) {
+        // decreasing offsets: the caller is told, and nothing is read by them
+        if (off[nsets] < off[0]) n = 0;
+        n = n >= tx.gram ? n - tx.gram + 1 : 0;
+    }
     // the last LK mod 64 functions: S slices of the items each
     const uint32_t full = LK & ~63u, rem = LK - full, S = rem ? 64 / rem : 1;
     const uint32_t rf = (uint32_t)lane / S, rs = (uint32_t)lane - rf * S;
@@ -248,9 +252,9 @@ void minhash_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, 
 }
 
 void hash_batch(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipStream_t s,
-                uint64_t *counters_host, Arena *ws) {
+                unsigned long long *ctr, Arena *ws) {
     if (is_dense(ix.p.family))
-        srp_hash(ix, in, codes_dev, s, counters_host, ws);
+        srp_hash(ix, in, codes_dev, s, ctr, ws);
     else
         minhash_hash(ix, in, codes_dev, s);
 }

@@ -984,6 +984,11 @@ __global__ void srp_zero_ctr_kernel(unsigned long long *ctr) {
     if (threadIdx.x < 2) ctr[threadIdx.x] = 0ull;
 }
 
+void zero_counters(unsigned long long *ctr, hipStream_t s) {
+    hipLaunchKernelGGL(srp_zero_ctr_kernel, dim3(1), dim3(64), 0, s, ctr);
+    FL_CHECK_LAUNCH();
+}
+
 size_t srp_scratch_bytes(const Index &ix, uint64_t n, const void *xdev) {
     const bool planes = !(xdev && srp_inplace(ix, xdev));
     if (ix.p.family != FLINNG_SRP_F32)
@@ -994,7 +999,7 @@ size_t srp_scratch_bytes(const Index &ix, uint64_t n, const void *xdev) {
 }
 
 void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipStream_t s,
-              uint64_t *counters_host, Arena *ws, float *proj_dev) {
+              unsigned long long *ctr, Arena *ws, float *proj_dev) {
     const uint64_t n = in.count;
     if (n == 0) return;
     const uint32_t d = ix.p.dim, dpad = ix.dpad;
@@ -1022,12 +1027,6 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
         // copy (zeros past d, which add nothing to any sum)
         const bool inplace = srp_inplace(ix, xdev);
         uint16_t *planes = sc.get<uint16_t>(inplace ? 0 : (size_t)n * dpad * 2);
-        // counters only when asked for (the kernel skips them otherwise)
-        unsigned long long *ctr = counters_host ? sc.get<unsigned long long>(16) : nullptr;
-        if (ctr) {
-            hipLaunchKernelGGL(srp_zero_ctr_kernel, dim3(1), dim3(64), 0, s, ctr);
-            FL_CHECK_LAUNCH();
-        }
         if (!inplace) {
             hipLaunchKernelGGL(prep_kernel<false>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s,
                                xdev, n, d, dpad, planes, nullptr, nullptr, nullptr, 0u, nullptr);
@@ -1044,13 +1043,6 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
             default: srp_launch_ks<4>(pl, a, s); break;
         }
         FL_CHECK_LAUNCH();
-        if (counters_host) {
-            unsigned long long c[2];
-            FL_HIP(hipMemcpyAsync(c, ctr, 16, hipMemcpyDeviceToHost, s));
-            FL_HIP(hipStreamSynchronize(s));
-            counters_host[0] = c[0];
-            counters_host[1] = c[1];
-        }
         return;
     }
 
@@ -1059,11 +1051,12 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
     float *nx = sc.get<float>(n * 4);
     uint32_t *bits = sc.get<uint32_t>(n * Hw * 4);
     uint32_t *flags = sc.get<uint32_t>(n * Hw * 4);
-    unsigned long long *ctr = sc.get<unsigned long long>(16);
+    unsigned long long *own = sc.get<unsigned long long>(16);  // where no one counts
     hipLaunchKernelGGL(prep_kernel<true>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, xdev, n,
-                       d, dpad, planes, nx, bits, flags, Hw, ctr);
+                       d, dpad, planes, nx, bits, flags, Hw, ctr ? nullptr : own);
     FL_CHECK_LAUNCH();
     constexpr int MR = 4, NR = 4, WM = 2, WN = 2;
+    if (!ctr) ctr = own;
     dim3 grid((H + 16 * NR * WN - 1) / (16 * NR * WN),
               (unsigned)((n + 16 * MR * WM - 1) / (16 * MR * WM)));
     hipLaunchKernelGGL((srp_mfma_kernel<MR, NR, WM, WN, 3>), grid, dim3(64 * WM * WN), 0, s,
@@ -1075,13 +1068,6 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
                        4 * Hw * sizeof(uint32_t), s, xdev, 1, n, d, ix.hyp, dpad, bits, flags, Hw,
                        H, K, L, codes_dev, ctr + 1);
     FL_CHECK_LAUNCH();
-    if (counters_host) {
-        unsigned long long c[2];
-        FL_HIP(hipMemcpyAsync(c, ctr, 16, hipMemcpyDeviceToHost, s));
-        FL_HIP(hipStreamSynchronize(s));
-        counters_host[0] = c[0];
-        counters_host[1] = c[1];
-    }
 }
 
 }  // namespace flinng

@@ -527,16 +527,17 @@ __global__ void merge_offsets_kernel(const uint32_t *__restrict__ ooff,
 
 unsigned blocks_for(uint64_t n, uint32_t per) { return (unsigned)((n + per - 1) / per); }
 
-struct HipFree {
-    void operator()(void *p) const { (void)hipFree(p); }
+// An index array in the making: freed, once the device is idle, unless
+// released.
+struct MemFree {
+    void operator()(void *p) const {
+        (void)hipDeviceSynchronize();
+        pool_free(p);
+    }
 };
-using HipMem = std::unique_ptr<void, HipFree>;
+using HipMem = std::unique_ptr<void, MemFree>;
 
-HipMem hip_mem(size_t bytes) {
-    void *p = nullptr;
-    FL_HIP(hipMalloc(&p, std::max<size_t>(bytes, 1)));
-    return HipMem(p);
-}
+HipMem hip_mem(size_t bytes, hipStream_t s) { return HipMem(pool_malloc(std::max<size_t>(bytes, 1), s)); }
 
 // What one batch of tables runs on.
 struct Batch {
@@ -596,7 +597,7 @@ __global__ void zero_tail_kernel(unsigned char *p, uint64_t a, uint64_t b) {
 }
 
 HipMem cells_with_tail(uint64_t entries, size_t csz, hipStream_t s) {
-    HipMem m = hip_mem(cells_alloc_bytes(entries, csz));
+    HipMem m = hip_mem(cells_alloc_bytes(entries, csz), s);
     hipLaunchKernelGGL(zero_tail_kernel, dim3(1), dim3(64), 0, s,
                        static_cast<unsigned char *>(m.get()), entries * csz,
                        (uint64_t)cells_alloc_bytes(entries, csz));
@@ -607,8 +608,9 @@ HipMem cells_with_tail(uint64_t entries, size_t csz, hipStream_t s) {
 }  // namespace
 
 void free_lists(Lists &l) {
-    if (l.offsets) (void)hipFree(l.offsets);
-    if (l.cells) (void)hipFree(l.cells);
+    if (l.offsets || l.cells) (void)hipDeviceSynchronize();
+    pool_free(l.offsets);
+    pool_free(l.cells);
     l = Lists();
 }
 
@@ -631,10 +633,10 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
     const uint64_t nblk = (nbk + 1 + n + OB_BLOCK - 1) / OB_BLOCK;
 
     Lists out;
-    HipMem offsets = hip_mem((size_t)L * (nbk + 1) * 4);
+    HipMem offsets = hip_mem((size_t)L * (nbk + 1) * 4, s);
     std::vector<std::pair<HipMem, uint64_t>> parts;  // the batches' cells
-    size_t need = 0;
-    auto piece = [&](size_t bytes) { const size_t o = need; need += Arena::round(bytes); return o; };
+    Pieces pc;
+    auto piece = [&](size_t bytes) { return pc.add(bytes); };
     const size_t o_pairs = piece((size_t)bt * n * 8), o_tmp = piece((size_t)stn * n * 8);
     const size_t o_pos = piece((size_t)bt * n * 4);
     const size_t o_longs = piece((size_t)bt * (n / (RUN_SHORT + 1) + 1) * 8);
@@ -642,7 +644,7 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
     const size_t o_blo = piece((size_t)bt * (nblk + 1) * 8);
     const size_t o_ps = piece(pair_sort_scratch_bytes(n, stn));
     const size_t o_scan = piece(scan_scratch_bytes((uint64_t)bt * n));
-    DevBuf ws(need, s);
+    DevBuf ws = DevBuf::pooled(pc.total, s);
     char *w = ws.as<char>();
     const Batch b{reinterpret_cast<uint64_t *>(w + o_pairs), reinterpret_cast<uint32_t *>(w + o_pos),
                   reinterpret_cast<uint64_t *>(w + o_longs), reinterpret_cast<unsigned int *>(w + o_nlong),
@@ -717,26 +719,33 @@ void merge_into(const Index &ix, Lists &d, Lists &out, hipStream_t s) {
     const uint64_t nbk = nbuckets(ix), no = (uint64_t)ix.p.L * (nbk + 1), nd = d.entries;
     const CellT *dc = static_cast<const CellT *>(d.cells);
     const CellT *oc = static_cast<const CellT *>(ix.cells);
-    DevBuf rank((nd + 1) * 4, s), before((nd + 1) * 4, s), total(8, s), sc(scan_scratch_bytes(nd), s);
-    DevBuf at((nd + 1) * 4, s), ac((nd + 1) * sizeof(CellT), s);
-    uint32_t *rk = rank.as<uint32_t>();
+    Pieces pc;
+    const size_t o_rank = pc.add((nd + 1) * 4), o_before = pc.add((nd + 1) * 4), o_at = pc.add((nd + 1) * 4),
+                 o_ac = pc.add((nd + 1) * sizeof(CellT)), o_total = pc.add(8),
+                 o_sc = pc.add(scan_scratch_bytes(nd));
+    DevBuf ws = DevBuf::pooled(pc.total, s);
+    char *w = ws.as<char>();
+    uint32_t *rk = reinterpret_cast<uint32_t *>(w + o_rank), *before = reinterpret_cast<uint32_t *>(w + o_before);
+    uint32_t *at = reinterpret_cast<uint32_t *>(w + o_at);
+    CellT *ac = reinterpret_cast<CellT *>(w + o_ac);
+    uint64_t *total = reinterpret_cast<uint64_t *>(w + o_total);
     if (nd) {
         hipLaunchKernelGGL(added_cells_kernel<CellT>, dim3(blocks_for(nd, 256)), dim3(256), 0, s,
-                           d.offsets, dc, nd, ix.offsets, oc, ix.p.L, nbk, rk, before.as<uint32_t>());
+                           d.offsets, dc, nd, ix.offsets, oc, ix.p.L, nbk, rk, before);
         FL_CHECK_LAUNCH();
     }
-    device_exclusive_scan_u32(rk, nd, 0, total.as<uint64_t>(), sc.ptr, s);
+    device_exclusive_scan_u32(rk, nd, 0, total, w + o_sc, s);
     if (nd) {
         hipLaunchKernelGGL(pack_added_kernel<CellT>, dim3(blocks_for(nd, 256)), dim3(256), 0, s, dc,
-                           before.as<uint32_t>(), rk, nd, total.as<uint64_t>(), at.as<uint32_t>(),
-                           ac.as<CellT>());
+                           before, rk, nd, total, at,
+                           ac);
         FL_CHECK_LAUNCH();
     }
     uint64_t nadd = 0;
-    FL_HIP(hipMemcpyAsync(&nadd, total.ptr, 8, hipMemcpyDeviceToHost, s));
-    FL_HIP(hipMalloc(&out.offsets, no * 4));
+    FL_HIP(hipMemcpyAsync(&nadd, total, 8, hipMemcpyDeviceToHost, s));
+    out.offsets = static_cast<uint32_t *>(pool_malloc(no * 4, s));
     hipLaunchKernelGGL(merge_offsets_kernel, dim3(blocks_for(no, 256)), dim3(256), 0, s, ix.offsets,
-                       d.offsets, rk, nd, total.as<uint64_t>(), no, out.offsets);
+                       d.offsets, rk, nd, total, no, out.offsets);
     FL_CHECK_LAUNCH();
     FL_HIP(hipStreamSynchronize(s));
     out.entries = ix.list_entries + nadd;
@@ -744,7 +753,7 @@ void merge_into(const Index &ix, Lists &d, Lists &out, hipStream_t s) {
     HipMem cells = cells_with_tail(out.entries, sizeof(CellT), s);
     if (out.entries) {
         hipLaunchKernelGGL(merge_cells_kernel<CellT>, dim3(blocks_for(out.entries, MG_TILE)), dim3(256),
-                           0, s, oc, at.as<uint32_t>(), ac.as<CellT>(), nadd, out.entries,
+                           0, s, oc, at, ac, nadd, out.entries,
                            static_cast<CellT *>(cells.get()));
         FL_CHECK_LAUNCH();
     }
