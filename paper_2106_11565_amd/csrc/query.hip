@@ -1139,7 +1139,11 @@ static uint32_t cap_for(uint32_t k, int T) {
 
 static int max_lds();
 
-// Launch shape of the query kernel for one index and k.
+// Batches up to these sizes take 1024-thread workgroups whatever their state's
+// size (fast decode, general k).
+constexpr uint64_t WIDE_FAST = 64, WIDE_GENERAL = 1024;
+
+// Launch shape of the query kernel for one index, k and batch size.
 struct QShape {
     int T;
     uint32_t cap, hc;
@@ -1152,30 +1156,40 @@ struct QShape {
 // of one workgroup has left, up to HC_MAX.
 // sparse: the index's lists are short enough that its queries are expected
 // to count sparsely, with the histogram built while counting (no copies).
-static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool sparse) {
+static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool sparse, uint64_t nq,
+                      double mean_entries) {
     const size_t lim = (size_t)max_lds();
     const size_t bins = (size_t)R * (L + 1) * 4;
     QShape sh;
     const bool gk = k > 64;
     const size_t small = q_layout(L, R, Bp, cap_for(k, 256), 256, 1, gk).total;
-    if (small * 4 <= lim) {
+    const size_t big = q_layout(L, R, Bp, cap_for(k, 1024), 1024, 1, gk).total;
+    // small batches of queries with some work in them: 256-thread workgroups
+    // would leave the chip part empty and the slowest query decides, so each
+    // gets 1024 threads (517 queries, k = 100, 21,000 entries each: 743 -> 300
+    // us; 30 queries, k = 10, thousands of entries: 119 -> 36 us a call; one of
+    // 74 entries stays at 16 us with 256 threads and would take 20)
+    const bool wide = nq <= (gk ? WIDE_GENERAL : WIDE_FAST) && mean_entries >= 512.0 && big <= lim;
+    if (small * 4 <= lim && !wide) {
         // a state this small holds few cells, so few counts collide: four
         // copies (more only add clearing and merging), none for sparse
         // queries, whose smaller state may then let one more workgroup in
         sh.T = 256;
         sh.hc = sparse ? 1u : (uint32_t)std::min<size_t>(4, 1 + (lim / 4 - small) / bins);
     } else {
-        const size_t big = q_layout(L, R, Bp, cap_for(k, 1024), 1024, 1, gk).total;
         sh.T = big <= lim ? 1024 : 256;
         sh.hc = big <= lim ? (uint32_t)std::min<size_t>(HC_MAX, 1 + (lim - big) / bins) : 1u;
     }
     while (sh.hc & (sh.hc - 1)) sh.hc &= sh.hc - 1;  // round down to a power of two
     sh.cap = cap_for(k, sh.T);
     // general k: up to four appends per thread and round where the workgroup's
-    // share of the LDS has the room
+    // share of the LDS has the room; two where queries meet few entries (many of
+    // them then end in a pass that keeps every member, and a larger buffer
+    // tightens its threshold later and takes longer to sort: 5,000 reads, k =
+    // 100, 176 us against 227)
     if (gk) {
         const size_t share = sh.T == 256 && small * 4 <= lim ? lim / 4 : lim;
-        while (sh.cap < k + 4u * (uint32_t)sh.T &&
+        while (sh.cap < k + (mean_entries < 512.0 ? 2u : 4u) * (uint32_t)sh.T &&
                q_layout(L, R, Bp, sh.cap * 2, sh.T, 1, gk).total <= share)
             sh.cap *= 2;
         while (sh.hc > 1 && q_layout(L, R, Bp, sh.cap, sh.T, sh.hc, gk).total > share) sh.hc >>= 1;
@@ -1191,11 +1205,6 @@ static bool sparse_index(const Index &ix) {
     const uint32_t Bp = (ix.p.B + 3) & ~3u;
     const uint64_t words = ((uint64_t)ix.p.R * Bp) / 4;
     return (ix.list_entries >> ix.nbits) * 4 <= words;
-}
-
-size_t query_lds_bytes(const Index &ix, uint32_t k) {
-    const uint32_t Bp = (ix.p.B + 3) & ~3u;
-    return q_shape(ix.p.L, ix.p.R, Bp, k, sparse_index(ix)).lds;
 }
 
 // Device attributes read once per process (function-local statics are
@@ -1319,7 +1328,7 @@ static QArgs make_args(const Index &ix, const uint32_t *codes, uint64_t nq, uint
     a.Bp = (ix.p.B + 3) & ~3u;
     a.nbits = ix.nbits;
     a.k = k;
-    const QShape sh = q_shape(a.L, a.R, a.Bp, k, sparse_index(ix));
+    const QShape sh = q_shape(a.L, a.R, a.Bp, k, sparse_index(ix), nq, ix.mean_entries);
     a.threads = (uint32_t)sh.T;
     a.cap = sh.cap;
     a.hc = sh.hc;

@@ -45,6 +45,19 @@ def test_general_k_equals_oracle(fl, N, R, B, K, L):
             assert np.array_equal(got[1], want[1]), (k, pers)
 
 
+@pytest.mark.parametrize("nq,k", [(64, 10), (65, 10), (1024, 65), (1025, 65)])
+@pytest.mark.parametrize("K", [4, 14])  # many and few list entries per query
+def test_batch_sizes_around_the_workgroup_rule(fl, nq, k, K):
+    X, Q, _ = synth.dense_gmm(N=8000, d=16, n_centres=30, sigma=0.2, nq=nq)
+    gi = fl.Index(X, 0, K, 10, 3, 64, seed=79)
+    oi = oracle.OracleIndex(oracle.SRP_F32, X, K, 10, 3, 64, 79)
+    want = oi.query(Q, k)
+    for pers in (False, True):
+        log("batch size", nq, "k", k, "K", K, "persistent", pers)
+        got = gi.query(Q, k, persistent=pers)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), pers
+
+
 def _sets(vals):
     return np.asarray(vals, dtype=np.uint32), np.arange(len(vals) + 1, dtype=np.uint64)
 
