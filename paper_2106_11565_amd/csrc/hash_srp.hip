@@ -436,7 +436,8 @@ __global__ __launch_bounds__(256) void srp_recheck_pack_kernel(
 // wavefronts: column wavefront c owns the group's hyperplanes 48c .. 48c+47
 // (MR x 3 MFMA tiles of 16 x 16, v_mfma_f32_16x16x32_bf16), and each of the
 // KS k groups of NW wavefronts takes one contiguous run of whole 128-wide k
-// chunks.  A group walks its run in 64-wide steps: its rows are staged once
+// chunks.  A group walks its run in LK-wide steps (64, or for large batches a
+// whole chunk, which keeps no partials from step to step): its rows are staged once
 // in LDS (double-buffered, rows padded by 16 bytes against bank conflicts)
 // and multiplied by its NW wavefronts, while each wavefront reads its own
 // hyperplanes' fragments straight from global memory (no other wavefront of
@@ -467,8 +468,6 @@ __global__ __launch_bounds__(256) void srp_recheck_pack_kernel(
 // Workgroup order: the hardware hands consecutive workgroup ids to the eight
 // XCDs in turn; ids are renumbered so that the groups of one row tile (which
 // read the same rows) run on one XCD, close in time, and share its L2.
-constexpr int LK = 64;        // k per pipeline step (two 32-wide MFMA slices)
-constexpr int LROW = LK + 8;  // bf16 per LDS row (16 bytes of padding)
 constexpr int LCHK = 128;     // k per accumulation chunk
 constexpr int FW = 48;        // hyperplanes per wavefront
 constexpr int FMAXW = 6;      // column wavefronts per workgroup at most
@@ -481,8 +480,9 @@ inline uint32_t srp_lds_terms(uint32_t dpad) {
 }
 
 // Sizes of one srp_fused_kernel variant.
-template <int MR, int NW, int KS>
+template <int MR, int NW, int KS, int LK>
 struct FusedShape {
+    static constexpr int LROW = LK + 8;             // bf16 per LDS row (16 bytes of padding)
     static constexpr int TM = 16 * MR;
     static constexpr int GT = 64 * NW;              // threads of one k group
     static constexpr int XP = TM * LK / 8;          // 16-byte pieces of one step's rows
@@ -493,13 +493,14 @@ struct FusedShape {
     static constexpr size_t LDS = XBYTES > PBYTES ? XBYTES : PBYTES;      // dynamic LDS
 };
 
-template <int MR, int NW, int KS>
+template <int MR, int NW, int KS, int LK>
 __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
     const uint16_t *__restrict__ x, uint32_t ld, uint32_t d, const uint16_t *__restrict__ w,
     const uint16_t *__restrict__ wt, uint32_t dpad, const float *__restrict__ nw, uint64_t n,
     uint32_t K, uint32_t L, uint32_t gt, float gamma, float tau_abs, uint32_t *__restrict__ codes,
     unsigned long long *__restrict__ ctr, float *__restrict__ proj) {
-    using SH = FusedShape<MR, NW, KS>;
+    using SH = FusedShape<MR, NW, KS, LK>;
+    constexpr int LROW = SH::LROW, LP = LK / 8, LS = LK / 32;  // pieces and slices of a step
     constexpr int TM = SH::TM, GT = SH::GT, XP = SH::XP, PPT = SH::PPT, XB = SH::XB;
     constexpr int NWV = NW * KS;
     // row buffers during the k loop, then the group sums (fp32)
@@ -538,14 +539,15 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
     const uint32_t kmax = cpg * LCHK < d ? cpg * LCHK : d;
     const uint32_t nmax = (kmax + LK - 1) / LK;
 
-    // this thread's pieces of the rows: piece p covers tile row p / 8, k
-    // offset 8 * (p % 8) of the step (rows past n clamped, never output)
-    const uint16_t *xp[PPT];
+    // this thread's pieces of the rows: piece p covers tile row p / LP,
+    // k offset 8 * (p % LP) of the step (rows past n clamped, never output)
+    const uint16_t *xt = x + r0 * ld;
+    uint32_t xo[PPT];  // within the tile's rows
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const uint32_t p = gtid + GT * j;
-        const uint64_t r = (p < XP && r0 + p / 8 < n) ? r0 + p / 8 : n - 1;
-        xp[j] = x + r * ld + 8 * (p % 8);
+        const uint32_t r = (p < XP && r0 + p / LP < n) ? p / LP : (uint32_t)(n - 1 - r0);
+        xo[j] = r * ld + 8 * (p % LP);
     }
     // this lane's hyperplanes: column 16b + lane % 16 of the wavefront's 48
     // (clamped into the group; the clamped columns' outputs are unused), read
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
     uint16_t *sx = sxa + kg * 2 * XB;  // this group's two row buffers
 
     uint4 xr[PPT];
-    uint4 wf[2][3], wn[2][3];
+    uint4 wf[LS][3], wn[LS][3];
     double ss[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) ss[j] = 0.0;
@@ -570,13 +572,13 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             const uint32_t p = gtid + GT * j;
-            const bool in = p < XP && k0 + 8 * (p % 8) < ke;
-            xr[j] = in ? *reinterpret_cast<const uint4 *>(xp[j] + k0) : uint4{0u, 0u, 0u, 0u};
+            const bool in = p < XP && k0 + 8 * (p % LP) < ke;
+            xr[j] = in ? *reinterpret_cast<const uint4 *>(xt + (xo[j] + k0)) : uint4{0u, 0u, 0u, 0u};
         }
     };
-    auto fetch_w = [&](uint32_t k0, uint4(&f)[2][3]) {
+    auto fetch_w = [&](uint32_t k0, uint4(&f)[LS][3]) {
 #pragma unroll
-        for (int hs = 0; hs < 2; ++hs) {
+        for (int hs = 0; hs < LS; ++hs) {
             const bool in = k0 + 32 * hs < ke;
 #pragma unroll
             for (int b = 0; b < 3; ++b)
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
         for (int j = 0; j < PPT; ++j) {
             const uint32_t p = gtid + GT * j;
             if (p < XP) {
-                *reinterpret_cast<uint4 *>(&sx[buf * XB + (p / 8) * LROW + 8 * (p % 8)]) = xr[j];
+                *reinterpret_cast<uint4 *>(&sx[buf * XB + (p / LP) * LROW + 8 * (p % LP)]) = xr[j];
                 const uint32_t v[4] = {xr[j].x, xr[j].y, xr[j].z, xr[j].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -605,6 +607,13 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
         fetch_x(kb);
         fetch_w(kb, wf);
         stage(0);
+        // waited for here: left in flight, the first step's fragments make the
+        // compiler wait in every step, and there for the next step's loads too
+#pragma unroll
+        for (int hs = 0; hs < LS; ++hs)
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                asm volatile("" : "+v"(wf[hs][b].x), "+v"(wf[hs][b].y), "+v"(wf[hs][b].z), "+v"(wf[hs][b].w));
     }
     __syncthreads();
 
@@ -627,46 +636,72 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
         }
         if (act) {
             const uint16_t *cx = sx + (st & 1) * XB;
+            if constexpr (LK == LCHK) {
+                // a step is a chunk: a row block's partials live for its 12 MFMAs
 #pragma unroll
-            for (int hs = 0; hs < 2; ++hs) {
-                if (k0 + 32 * hs < ke) {  // uniform: ke is a multiple of 32
-                    bf16x8 fa[MR];
+                for (int a = 0; a < MR; ++a) {
+                    bf16x8 fa[LS];
+                    f32x4 c[3];
 #pragma unroll
-                    for (int a = 0; a < MR; ++a)
-                        fa[a] = __builtin_bit_cast(
+                    for (int hs = 0; hs < LS; ++hs)
+                        fa[hs] = __builtin_bit_cast(
                             bf16x8,
                             *reinterpret_cast<const uint4 *>(&cx[(16 * a + lr) * LROW + 32 * hs + lk]));
 #pragma unroll
-                    for (int a = 0; a < MR; ++a)
+                    for (int b = 0; b < 3; ++b) c[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int hs = 0; hs < LS; ++hs)  // (slices past d hold zeros)
 #pragma unroll
                         for (int b = 0; b < 3; ++b)
-                            prt[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                fa[a], __builtin_bit_cast(bf16x8, wf[hs][b]), prt[a][b], 0, 0, 0);
+                            c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                fa[hs], __builtin_bit_cast(bf16x8, wf[hs][b]), c[b], 0, 0, 0);
+#pragma unroll
+                    for (int b = 0; b < 3; ++b)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[a][b][i] += c[b][i];
                 }
-            }
-            if ((k0 + LK - kb) % LCHK == 0 || !more) {
-                // close the chunk: one fp32 addition per output
-#pragma unroll
-                for (int a = 0; a < MR; ++a)
-#pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[a][b][i] += prt[a][b][i];
-                        prt[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            } else {
+    #pragma unroll
+                for (int hs = 0; hs < LS; ++hs) {
+                    if (k0 + 32 * hs < ke) {  // uniform: ke is a multiple of 32
+                        bf16x8 fa[MR];
+    #pragma unroll
+                        for (int a = 0; a < MR; ++a)
+                            fa[a] = __builtin_bit_cast(
+                                bf16x8,
+                                *reinterpret_cast<const uint4 *>(&cx[(16 * a + lr) * LROW + 32 * hs + lk]));
+    #pragma unroll
+                        for (int a = 0; a < MR; ++a)
+    #pragma unroll
+                            for (int b = 0; b < 3; ++b)
+                                prt[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    fa[a], __builtin_bit_cast(bf16x8, wf[hs][b]), prt[a][b], 0, 0, 0);
                     }
+                }
+                if ((k0 + LK - kb) % LCHK == 0 || !more) {
+                    // close the chunk: one fp32 addition per output
+    #pragma unroll
+                    for (int a = 0; a < MR; ++a)
+    #pragma unroll
+                        for (int b = 0; b < 3; ++b) {
+    #pragma unroll
+                            for (int i = 0; i < 4; ++i) acc[a][b][i] += prt[a][b][i];
+                            prt[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        }
+                }
             }
         }
         if (more) {
             stage((st + 1) & 1);
 #pragma unroll
-            for (int hs = 0; hs < 2; ++hs)
+            for (int hs = 0; hs < LS; ++hs)
 #pragma unroll
                 for (int b = 0; b < 3; ++b) wf[hs][b] = wn[hs][b];
         }
         __syncthreads();
     }
 
-    // row norms: the 8 lanes holding one row's pieces are adjacent; the
+    // row norms: the LP lanes holding one row's pieces are adjacent; the
     // groups' sums are added in group order
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
@@ -674,8 +709,9 @@ __global__ __launch_bounds__(64 * NW * KS) void srp_fused_kernel(
         v += __shfl_xor(v, 1, 64);
         v += __shfl_xor(v, 2, 64);
         v += __shfl_xor(v, 4, 64);
+        if (LP > 8) v += __shfl_xor(v, 8, 64);
         const uint32_t p = gtid + GT * j;
-        if (p < XP && p % 8 == 0) snx2[kg * TM + p / 8] = v;
+        if (p < XP && p % LP == 0) snx2[kg * TM + p / LP] = v;
     }
     // the group sums (the row buffers are free: every group left the loop)
     if (KS > 1 && kg > 0) {
@@ -857,10 +893,21 @@ static bool srp_inplace(const Index &ix, const void *xdev) {
 // groups of a tile run on one XCD and share its L2) and the hyperplanes once
 // per workgroup; plus a fixed 4 us.  Within 2% the plan with more workgroups
 // wins.  KS needs nch >= 2 KS (the rounding bound).
+// Large batches take tiles of 96 rows against up to 288 hyperplanes, a whole
+// chunk per step (WIDE_*): the rows cross the L2 once instead of once per 96
+// hyperplanes and the hyperplanes two thirds as often.  About 4.2 us per round
+// of 256 workgroups and chunk, and 15% is asked for: the model above, fitted
+// before the first step's loads were waited for outside the loop, is that much
+// too high (65,536 rows, d = 4096, 288 hyperplanes: 520 us then, 451 now, 400
+// with the wide tile; 10,000 rows: 100, 91 and 152).  Only from 8 chunks on, so
+// that the steps outweigh the filling and the epilogue.
+constexpr int WIDE_MR = 6, WIDE_LK = LCHK;
+constexpr uint32_t WIDE_NCH = 8;
 struct SrpPlan {
     int mr, nw, ks;
     uint32_t gt;
     uint64_t wgs;
+    int lk;
 };
 
 // The compiled variants: KS = 8 only with one column wavefront and tiles of
@@ -875,7 +922,7 @@ static SrpPlan srp_plan(uint32_t K, uint32_t L, uint64_t n, uint32_t d) {
     static const int KSS[] = {1, 2, 4, 8};
     const double A = 0.2e-6, B = 0.1e-6, C = 0.04, BWG = 10e12, FIX = 4e-6;
     const uint32_t nch = (d + LCHK - 1) / LCHK;
-    SrpPlan best{4, FMAXW, 1, 1, 0};
+    SrpPlan best{4, FMAXW, 1, 1, 0, 64};
     double best_t = -1.0;
     for (int mr : MRS) {
         const uint64_t tm = 16 * (uint64_t)mr, nrt = (n + tm - 1) / tm;
@@ -904,11 +951,20 @@ static SrpPlan srp_plan(uint32_t K, uint32_t L, uint64_t n, uint32_t d) {
                 // within 2% of the best so far, the plan with more workgroups
                 // (the bandwidth bound ties plans the traces tell apart)
                 if (best_t < 0.0 || t < 0.98 * best_t || (t <= 1.02 * best_t && wgs > best.wgs)) {
-                    best = SrpPlan{mr, nw, ks, gt, wgs};
+                    best = SrpPlan{mr, nw, ks, gt, wgs, 64};
                     best_t = t;
                 }
             }
         }
+    }
+    if (nch >= WIDE_NCH) {
+        uint32_t gt = std::min(L, (uint32_t)FMAXH / K);
+        const uint32_t ng = (L + gt - 1) / gt;
+        gt = (L + ng - 1) / ng;
+        const uint64_t tm = 16 * WIDE_MR, nrt = (n + tm - 1) / tm, wgs = nrt * ng;
+        const double bytes = 2.0 * d * (double)(nrt * tm + wgs * (uint64_t)FMAXH);
+        const double t = std::max((double)((wgs + 255) / 256) * nch * 4.2e-6, bytes / BWG) + FIX;
+        if (t < 0.85 * best_t) best = SrpPlan{WIDE_MR, FMAXW, 1, gt, wgs, WIDE_LK};
     }
     return best;
 }
@@ -924,19 +980,19 @@ struct SrpFusedArgs {
     float *proj;
 };
 
-template <int MR, int NW, int KS>
+template <int MR, int NW, int KS, int LK = 64>
 static void srp_launch(const SrpPlan &pl, const SrpFusedArgs &a, hipStream_t s) {
-    constexpr size_t lds = FusedShape<MR, NW, KS>::LDS;
+    constexpr size_t lds = FusedShape<MR, NW, KS, LK>::LDS;
     // once per variant and process (a throwing initialiser is retried)
     static const bool attrs_ok = [] {
-        const void *fn = reinterpret_cast<const void *>(&srp_fused_kernel<MR, NW, KS>);
+        const void *fn = reinterpret_cast<const void *>(&srp_fused_kernel<MR, NW, KS, LK>);
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
             hipSuccess)
             fail(FLINNG_EDEVICE, "SRP kernel: its LDS does not fit");
         return true;
     }();
     (void)attrs_ok;
-    hipLaunchKernelGGL((srp_fused_kernel<MR, NW, KS>), dim3((unsigned)pl.wgs), dim3(64 * NW * KS),
+    hipLaunchKernelGGL((srp_fused_kernel<MR, NW, KS, LK>), dim3((unsigned)pl.wgs), dim3(64 * NW * KS),
                        lds, s, a.x, a.ld, a.d, a.ix->hyp, a.ix->hypt, a.ix->dpad, a.ix->hypnorm, a.n,
                        a.ix->p.K, a.ix->p.L, pl.gt, a.gamma, a.tau_abs, a.codes, a.ctr, a.proj);
 }
@@ -1037,7 +1093,9 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
         const SrpFusedArgs a{inplace ? static_cast<const uint16_t *>(xdev) : planes,
                              dpad, dpad, &ix, n, gamma, tau_abs, codes_dev,
                              ctr, proj_dev};
-        switch (pl.mr) {
+        if (pl.lk == WIDE_LK)
+            srp_launch<WIDE_MR, FMAXW, 1, WIDE_LK>(pl, a, s);
+        else switch (pl.mr) {
             case 1: srp_launch_ks<1>(pl, a, s); break;
             case 2: srp_launch_ks<2>(pl, a, s); break;
             default: srp_launch_ks<4>(pl, a, s); break;
