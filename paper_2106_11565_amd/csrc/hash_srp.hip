@@ -195,6 +195,11 @@ __global__ void prep_kernel(const void *__restrict__ xin, uint64_t n, uint32_t d
 // consecutive k values at 8*(l/16) of each 32-wide k step, identically for
 // X and W, so every product pairs x[row][k] with w[col][k].
 // Output of a 16x16 tile: lane l holds rows 4*(l/16)+i, column l%16.
+// Bound by the latency of its loads (a few workgroups per compute unit at
+// most): two sets of fragments, so the 16 loads of the next 32 k are in flight
+// during the 48 products of these.  With one set the compiler waited for each
+// fragment in turn before its four products; a whole query call on 4,096 rows
+// of d = 768 went from 254 to 230 us.  The order of the products is unchanged.
 template <int MR, int NR, int WM, int WN, int NSPLIT>
 __global__ __launch_bounds__(64 * WM * WN) void srp_mfma_kernel(
     const uint16_t *__restrict__ planes, uint64_t plane_stride, uint32_t ld,
@@ -232,26 +237,41 @@ __global__ __launch_bounds__(64 * WM * WN) void srp_mfma_kernel(
         pb[b] = w + (uint64_t)c * dpad + lk;
     }
 
-    for (uint32_t k0 = 0; k0 < dpad; k0 += 32) {
-        bf16x8 fb[NR];
+    // the fragments of the next 32 k are loaded before this step's products
+    // (the last step loads its own again; nothing reads them)
+    uint4 fb[2][NR], fa[2][NSPLIT][MR];
+    auto fetch = [&](uint32_t k0, uint4(&xb)[NR], uint4(&xa)[NSPLIT][MR]) {
 #pragma unroll
-        for (int b = 0; b < NR; ++b)
-            fb[b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(pb[b] + k0));
+        for (int b = 0; b < NR; ++b) xb[b] = *reinterpret_cast<const uint4 *>(pb[b] + k0);
 #pragma unroll
-        for (int sp = 0; sp < NSPLIT; ++sp) {
-            bf16x8 fa[MR];
+        for (int sp = 0; sp < NSPLIT; ++sp)
 #pragma unroll
             for (int a = 0; a < MR; ++a)
-                fa[a] = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const uint4 *>(pa[a] + sp * plane_stride + k0));
+                xa[sp][a] = *reinterpret_cast<const uint4 *>(pa[a] + sp * plane_stride + k0);
+    };
+    auto product = [&](const uint4(&xb)[NR], const uint4(&xa)[NSPLIT][MR]) {
+#pragma unroll
+        for (int sp = 0; sp < NSPLIT; ++sp)
 #pragma unroll
             for (int a = 0; a < MR; ++a)
 #pragma unroll
                 for (int b = 0; b < NR; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b],
-                                                                        0, 0, 0);
-        }
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, xa[sp][a]), __builtin_bit_cast(bf16x8, xb[b]),
+                        acc[a][b], 0, 0, 0);
+    };
+    fetch(0, fb[0], fa[0]);
+    for (uint32_t k0 = 0; k0 + 64 <= dpad; k0 += 64) {
+        fetch(k0 + 32, fb[1], fa[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        product(fb[0], fa[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(k0 + 64 < dpad ? k0 + 64 : k0, fb[0], fa[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        product(fb[1], fa[1]);
+        __builtin_amdgcn_sched_barrier(0);
     }
+    if (dpad % 64) product(fb[0], fa[0]);
 
     // Epilogue: trusted sign bits and flags, 16 columns per ballot group.
     unsigned long long flagged = 0;
