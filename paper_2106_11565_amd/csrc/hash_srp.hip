@@ -378,9 +378,12 @@ __device__ int exact_sign_wave(const void *xin, bool f32, uint64_t row, uint32_t
 
 // Recheck + pack: one wavefront per row.  Bits of the row are staged in LDS
 // (Hw words), flagged projections are recomputed in FP64 across the wave,
-// then lanes t < L extract the K-bit code of table t.
+// then lanes t < L extract the K-bit code of table t.  Bound by latency (a row's
+// flagged projections in turn, each two loads per 64 values and a butterfly), so
+// eight pairs of loads are in flight per lane: a query call on 4,096 rows of
+// d = 768 went from 230 to 214 us, on 12,000 rows of d = 1,500 from 653 to 517.
 __global__ __launch_bounds__(256) void srp_recheck_pack_kernel(
-    const void *__restrict__ xin, int f32, uint64_t n, uint32_t d,
+    const float *__restrict__ x, uint64_t n, uint32_t d,
     const uint16_t *__restrict__ w, uint32_t dpad, const uint32_t *__restrict__ bits,
     const uint32_t *__restrict__ flags, uint32_t Hw, uint32_t H, uint32_t K, uint32_t L,
     uint32_t *__restrict__ codes, unsigned long long *__restrict__ nexact) {
@@ -390,6 +393,7 @@ __global__ __launch_bounds__(256) void srp_recheck_pack_kernel(
     const uint64_t row = (uint64_t)blockIdx.x * (blockDim.x / 64) + wave;
     if (row >= n) return;
     uint32_t *rb = sm + wave * Hw;
+    const float *xr = x + row * d;
     for (uint32_t j = lane; j < Hw; j += 64) rb[j] = bits[row * Hw + j];
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -407,12 +411,22 @@ __global__ __launch_bounds__(256) void srp_recheck_pack_kernel(
                 if (h >= H) continue;
                 const uint16_t *wh = w + (uint64_t)h * dpad;
                 double v = 0.0, a = 0.0;
-                for (uint32_t i = lane; i < d; i += 64) {
-                    double xv = f32 ? (double)static_cast<const float *>(xin)[row * d + i]
-                                    : (double)bf16_to_f32(static_cast<const uint16_t *>(xin)[row * d + i]);
-                    double p = xv * (double)bf16_to_f32(wh[i]);
-                    v += p;
-                    a += fabs(p);
+                // eight loads of each operand in flight (zeros past d add nothing)
+                for (uint32_t i0 = lane; i0 < d; i0 += 512) {
+                    float xs[8];
+                    uint16_t ws[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const uint32_t i = i0 + 64 * e;
+                        xs[e] = xr[i < d ? i : i0];
+                        ws[e] = wh[i < d ? i : i0];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const double p = i0 + 64 * e < d ? (double)xs[e] * (double)bf16_to_f32(ws[e]) : 0.0;
+                        v += p;
+                        a += fabs(p);
+                    }
                 }
                 v = wave_sum_f64(v);
                 a = wave_sum_f64(a);
@@ -422,7 +436,7 @@ __global__ __launch_bounds__(256) void srp_recheck_pack_kernel(
                 if (__builtin_amdgcn_readfirstlane(fabs(v) > 2.0 * (double)d * 0x1p-53 * a ? 1 : 0)) {
                     sgn = v > 0.0 ? 1 : -1;
                 } else {
-                    sgn = exact_sign_wave(xin, f32 != 0, row, d, d, wh);
+                    sgn = exact_sign_wave(x, true, row, d, d, wh);
                     if (lane == 0) atomicAdd(nexact, 1ull);
                 }
                 if (lane == 0) {
@@ -1143,7 +1157,7 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
                        reinterpret_cast<uint16_t *>(flags), ctr, proj_dev);
     FL_CHECK_LAUNCH();
     hipLaunchKernelGGL(srp_recheck_pack_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256),
-                       4 * Hw * sizeof(uint32_t), s, xdev, 1, n, d, ix.hyp, dpad, bits, flags, Hw,
+                       4 * Hw * sizeof(uint32_t), s, static_cast<const float *>(xdev), n, d, ix.hyp, dpad, bits, flags, Hw,
                        H, K, L, codes_dev, ctr + 1);
     FL_CHECK_LAUNCH();
 }
