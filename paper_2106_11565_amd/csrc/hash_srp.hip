@@ -930,13 +930,16 @@ static bool srp_inplace(const Index &ix, const void *xdev) {
 // Large batches take tiles of 96 rows against up to 288 hyperplanes, a whole
 // chunk per step (WIDE_*): the rows cross the L2 once instead of once per 96
 // hyperplanes and the hyperplanes two thirds as often.  About 4.2 us per round
-// of 256 workgroups and chunk, and 15% is asked for: the model above, fitted
-// before the first step's loads were waited for outside the loop, is that much
-// too high (65,536 rows, d = 4096, 288 hyperplanes: 520 us then, 451 now, 400
-// with the wide tile; 10,000 rows: 100, 91 and 152).  Only from 8 chunks on, so
+// of 256 workgroups and chunk.  The model above ranks the other tiles, but its
+// times for large batches are a third too low, so the wide tile is taken up to
+// WIDE_SCALE times its best.  Kernel, its choice against the wide tile: 24,576
+// rows, d = 4096, 288 hyperplanes 247 and 149 us; 49,000 rows, d = 2048 190 and
+// 154; 65,536 rows, d = 4096 473 and 447; 262,144 rows, d = 1024 522 and 514;
+// beyond the line, 10,000 rows, d = 4096: 91 and 152.  Only from 8 chunks on, so
 // that the steps outweigh the filling and the epilogue.
 constexpr int WIDE_MR = 6, WIDE_LK = LCHK;
 constexpr uint32_t WIDE_NCH = 8;
+constexpr double WIDE_SCALE = 1.38;
 struct SrpPlan {
     int mr, nw, ks;
     uint32_t gt;
@@ -998,7 +1001,7 @@ static SrpPlan srp_plan(uint32_t K, uint32_t L, uint64_t n, uint32_t d) {
         const uint64_t tm = 16 * WIDE_MR, nrt = (n + tm - 1) / tm, wgs = nrt * ng;
         const double bytes = 2.0 * d * (double)(nrt * tm + wgs * (uint64_t)FMAXH);
         const double t = std::max((double)((wgs + 255) / 256) * nch * 4.2e-6, bytes / BWG) + FIX;
-        if (t < 0.85 * best_t) best = SrpPlan{WIDE_MR, FMAXW, 1, gt, wgs, WIDE_LK};
+        if (t < WIDE_SCALE * best_t) best = SrpPlan{WIDE_MR, FMAXW, 1, gt, wgs, WIDE_LK};
     }
     return best;
 }

@@ -22,7 +22,7 @@ def fl():
 
 
 @pytest.mark.parametrize("n,d,K,L", [
-    (24_577, 1024, 24, 12),   # 288 hyperplanes, whole chunks
+    (24_575, 1024, 24, 12),   # 288 hyperplanes, whole chunks
     (24_481, 1032, 16, 17),   # 272 hyperplanes, padded rows, a chunk of 32
     (24_576, 1120, 13, 40),   # two groups of 20 tables
 ])
