@@ -807,7 +807,7 @@ def extensions(w, torch, fl, configs, steps, warmup, ref):
                                    "20-gram items extracted on the device, then the query path",
                            "ms_per_step": round(ms, 4), "qps": round(w.nq / (ms / 1e3), 1),
                            "identical_to_item_queries": same,
-                           "note": "each call reads two offsets back to size the item buffer"}
+                           "note": "each call checks the offsets while it hashes and reads the verdict back"}
     log(f"text queries: {out['text_queries']}")
     t = max(1, w.L // 2)
     cap = 64
