@@ -39,9 +39,10 @@ struct QArgs {
     uint32_t lstep;  // the largest power of two below L (1 for L = 1)
 };
 
-// In the first id of a query: the sparse kernel left it to the general one (no
-// point has this id, and the first id of an answered query is a point's).
-constexpr uint32_t DEFERRED = 0xFFFFFFFFu;
+// In the first id of a query: the sparse kernel left it to the general one, and
+// a workgroup of that has taken it (no point has these ids, and the first id of
+// an answered query is a point's).
+constexpr uint32_t DEFERRED = 0xFFFFFFFFu, CLAIMED = 0xFFFFFFFEu;
 
 // misc slots
 enum { M_Q = 0, M_BUFN, M_NGE, M_NALL, M_LEVEL, M_REP, M_KEEPALL, M_NEXT, M_THRLO,

@@ -90,3 +90,23 @@ def test_every_variant_equals_oracle(fl, T, R, B, L, copies, heavy):
         if step == 0:
             gi.insert(_sets(vals[n0:]))
             oi.insert(_sets(vals[n0:]))
+
+
+@pytest.mark.parametrize("R,B,L", [(4, 1000, 8), (8, 5000, 20)])
+@pytest.mark.parametrize("nq", [4097, 66001])  # one, and several chunks of 64 per workgroup
+@pytest.mark.parametrize("every", [1, 7, 64, 1001])
+def test_deferred_queries_of_large_batches(fl, R, B, L, nq, every):
+    """One query in `every` is deferred: runs of them, one in each chunk that
+    the workgroups share, and few."""
+    rng = np.random.default_rng(nq + every)
+    n = 10000
+    vals = np.arange(n, dtype=np.uint64)
+    vals[rng.permutation(n)[:80]] = 10**6
+    vals = _value(vals)
+    gi = fl.Index(_sets(vals), fl.MINHASH_U32, 1, L, R, B, seed=4, bucket_bits=20)
+    assert _entries(gi, _value([10**6]))[0] > 1024 and _entries(gi, vals[:2000]).mean() < 370
+    q = np.concatenate([vals[:200], _value([10**6])])
+    small = gi.query(_sets(q), 10)  # too few for the sparse kernel
+    pick = np.where(np.arange(nq) % every == every // 2, 200, np.arange(nq) % 200)
+    got = gi.query(_sets(q[pick]), 10)
+    assert np.array_equal(got[0], small[0][pick]) and np.array_equal(got[1], small[1][pick])
