@@ -489,16 +489,19 @@ void launch_te(QArgs &a, uint32_t cell_bytes, hipStream_t s) {
 //     take 92 us in the general kernel and were twice that here;
 //   - batches that the general kernel takes in one or two rounds of workgroups
 //     (eight on a compute unit of 256 threads, one of 1024): the slowest query
-//     is then most of what there is to wait for, and the second launch (4 us to
-//     find nothing deferred) only adds to it.
+//     is then most of what there is to wait for, and the second launch (5-6 us to
+//     find nothing deferred) only adds to it;
+//   - batches whose launch, a workgroup per query, would have 2^32 threads: the
+//     runtime refuses such a grid, the persistent one takes any batch.
 int sparse_variant(const Index &ix, const QArgs &a) {
     if (a.k > 64 || (uint64_t)a.B * a.mstride >= (1ull << 32) || a.gmax > 65536) return 0;
     if (a.nq < (a.threads == 1024 ? 384 : 4096)) return 0;
     const double m = ix.mean_entries;
-    if (m <= 0.4 * 1024 && a.L <= 128) return 1;
+    auto fits = [&](int threads) { return a.nq * threads < (1ull << 32); };
+    if (m <= 0.4 * 1024 && a.L <= 128) return fits(128) ? 1 : 0;
     if (a.threads != 1024) return 0;
-    if (m <= 0.4 * 4096) return 2;
-    if (m <= 0.6 * 8192) return 3;
+    if (m <= 0.4 * 4096) return fits(256) ? 2 : 0;
+    if (m <= 0.6 * 8192) return fits(512) ? 3 : 0;
     return 0;
 }
 

@@ -110,3 +110,39 @@ def test_deferred_queries_of_large_batches(fl, R, B, L, nq, every):
     pick = np.where(np.arange(nq) % every == every // 2, 200, np.arange(nq) % 200)
     got = gi.query(_sets(q[pick]), 10)
     assert np.array_equal(got[0], small[0][pick]) and np.array_equal(got[1], small[1][pick])
+
+
+@pytest.mark.parametrize("T,copies,R,B,L", [(128, 2, 2, 64, 4), (256, 10, 8, 8192, 10),
+                                            (512, 30, 8, 8192, 10)])
+def test_persistent_batches_at_the_grid_limit(fl, T, copies, R, B, L):
+    """A batch whose sparse launch, a workgroup per query, would reach 2^32
+    threads is answered by the persistent grid; one query fewer by the sparse
+    kernel.  The answers are those of the same queries in a small batch."""
+    import ctypes
+    import torch
+    n = max(300 * copies, B)
+    vals = (np.arange(n, dtype=np.uint64) % (n // copies)) * 2654435761 % 2**32
+    ix = fl.Index(_sets(vals), fl.MINHASH_U32, 1, L, R, B, seed=13, bucket_bits=20)
+    met = _entries(ix, vals[:300]).mean()
+    assert 1.1 * RULES[T][0] <= met <= 0.9 * RULES[T][1]
+    base = torch.from_numpy(ix.debug_hash(_sets(vals[:300])).view(np.int32)).cuda()
+
+    def run(codes):
+        nq = codes.shape[0]
+        ids = torch.full((nq, 1), -7, dtype=torch.int32, device="cuda")
+        sc = torch.full((nq, 1), -7, dtype=torch.int32, device="cuda")
+        s = torch.cuda.current_stream().cuda_stream
+        fl.check(fl.lib().flinng_query_codes(
+            ix.handle, ctypes.c_void_p(codes.data_ptr()), nq, 1, ctypes.c_void_p(ids.data_ptr()),
+            ctypes.c_void_p(sc.data_ptr()), 1, None, ctypes.c_void_p(s)))
+        torch.cuda.synchronize()
+        return ids, sc
+
+    want = run(base)
+    assert int(want[1].min()) == L
+    for nq in (2**32 // T - 1, 2**32 // T):
+        log("grid limit", T, "queries", nq, "entries", met)
+        rows = torch.arange(nq, device="cuda", dtype=torch.int32) % 300
+        got = run(base[rows.long()])
+        for g, w in zip(got, want):
+            assert torch.equal(g, w[rows.long()])
