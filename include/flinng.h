@@ -170,9 +170,12 @@ int flinng_query(const flinng_index *idx, const flinng_input *q, uint32_t k,
  * (flinng_text): the n-gram items are extracted and mixed on the device,
  * then hashed, indexed and queried exactly as the same items given as sets
  * (an index built from sets answers text queries and vice versa, when the
- * items agree).  For device text the calls read two offsets back to size
- * the item buffer.  FLINNG_EINVAL for a dense index, radix outside 2..256,
- * gram 0, radix^gram above 2^64, or what flinng_build / flinng_query reject.
+ * items agree).  For device text the calls read the first and last offset back,
+ * to refuse offsets that decrease: a query waits for them while the batch is
+ * hashed (so for the work queued on `stream` before it), and a refused one
+ * writes no output.  FLINNG_EINVAL for that, a dense index, radix outside
+ * 2..256, gram 0, radix^gram above 2^64, or what flinng_build / flinng_query
+ * reject.
  */
 int flinng_build_text(const flinng_params *p, const flinng_text *data,
                       void *stream, flinng_index **out);

@@ -472,9 +472,12 @@ struct ReadbackLease {
 // Scratch of a batch that is kept in its stream's region rather than allocated.
 constexpr size_t SMALL_SCRATCH = (size_t)1 << 20;
 
+// check: the offsets of a text batch on the device, on their way to the host;
+// waited for once the hashing is queued, and nothing is written to the outputs
+// of a batch that is refused.
 static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t k, uint32_t *ids,
                        uint32_t *scores, uint32_t out_on_device, uint32_t persistent,
-                       void *stream, const TextSource *text = nullptr) {
+                       void *stream, const TextSource *text = nullptr, ReadbackLease *check = nullptr) {
     require(idx != nullptr, "index is NULL");
     const Index &ix = *reinterpret_cast<const Index *>(idx);
     validate_input(q, ix.p.family, "queries");
@@ -504,6 +507,10 @@ static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t 
     uint32_t *work = static_cast<uint32_t *>(a.take(4));
     if (text) {
         minhash_hash_text(ix, *text, nq, codes, s);
+        if (check) {
+            check->wait();
+            require(check->r.host[1] >= check->r.host[0], "text offsets must be nondecreasing");
+        }
     } else if (all && dense) {
         flinng_input in = *q;
         if (host_rows) {
@@ -564,8 +571,8 @@ int flinng_query_text(const flinng_index *idx, const flinng_text *q, uint32_t k,
             query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx);
             return;
         }
-        // the first and last offset are read back while the batch is hashed
-        // (which reads no symbol where they decrease), and refused after
+        // the first and last offset are read back while the batch is hashed (which
+        // reads no symbol where they decrease)
         ReadbackLease rb(ix);
         FL_HIP(hipMemcpyAsync(rb.r.host, q->offsets, 8, hipMemcpyDeviceToHost, s));
         FL_HIP(hipMemcpyAsync(rb.r.host + 1, q->offsets + q->count, 8, hipMemcpyDeviceToHost, s));
@@ -573,9 +580,7 @@ int flinng_query_text(const flinng_index *idx, const flinng_text *q, uint32_t k,
         rb.pending = true;
         const TextSource tx = text_source(*q, 0, s, sc);
         const flinng_input sets{tx.symbols, tx.offsets, q->count, 1, 0};
-        query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx);
-        rb.wait();
-        require(rb.r.host[1] >= rb.r.host[0], "text offsets must be nondecreasing");
+        query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx, &rb);
     });
 }
 

@@ -138,3 +138,31 @@ def test_text_errors(fl):
     gd = fl.Index(X, fl.SRP_F32, 4, 3, 2, 5, seed=1)
     with pytest.raises(fl.FlinngError):
         gd.query_text(ex["queries"], (20, 4, 7), 5)
+
+
+@pytest.mark.parametrize("nq", [1, 500])
+def test_refused_text_leaves_the_outputs_alone(fl, nq):
+    """Device text whose last offset lies before the first is refused, and
+    nothing is written by such a call; the next one is answered."""
+    import torch
+    data, _, ex, fam, _, p = _workload("genome")
+    txt = (ex["gram"], ex["radix"], ex["key"])
+    gi = fl.Index(data, fam, p["K"], p["L"], p["R"], p["B"], seed=5, bucket_bits=p["b"])
+    sym, off = _dev_text(torch, _slice(ex["queries"], 0, min(nq, 150)))
+    sym, off = sym.repeat(4), torch.cat([off + i * off[-1] for i in range(4)])[:nq + 1].contiguous()
+    bad = off.flip(0).contiguous()
+    out = (torch.full((nq, 10), -7, dtype=torch.int32, device="cuda"),
+           torch.full((nq, 10), -8, dtype=torch.int32, device="cuda"))
+    for pers in (False, True):
+        with pytest.raises(fl.FlinngError) as e:
+            gi.query_text((sym, bad), txt, 10, persistent=pers, out=out)
+        assert e.value.code == fl.EINVAL
+        torch.cuda.synchronize()
+        assert int((out[0] != -7).sum()) == 0 and int((out[1] != -8).sum()) == 0
+    with pytest.raises(fl.FlinngError) as e:
+        fl.Index((sym, bad), fam, p["K"], p["L"], p["R"], 1, seed=5, bucket_bits=p["b"], text=txt)
+    assert e.value.code == fl.EINVAL
+    gi.query_text((sym, off), txt, 10, out=out)
+    want = gi.query_text((sym.cpu().numpy().view(np.uint8), off.cpu().numpy().view(np.uint64)), txt, 10)
+    assert np.array_equal(out[0].cpu().numpy().view(np.uint32), want[0])
+    assert np.array_equal(out[1].cpu().numpy().view(np.uint32), want[1])
