@@ -173,9 +173,9 @@ int flinng_query(const flinng_index *idx, const flinng_input *q, uint32_t k,
  * items agree).  For device text the calls read the first and last offset back,
  * to refuse offsets that decrease: a query waits for them while the batch is
  * hashed (so for the work queued on `stream` before it), and a refused one
- * writes no output.  FLINNG_EINVAL for that, a dense index, radix outside
- * 2..256, gram 0, radix^gram above 2^64, or what flinng_build / flinng_query
- * reject.
+ * writes no output.  FLINNG_EINVAL for that, device text queried under stream
+ * capture, a dense index, radix outside 2..256, gram 0, radix^gram above 2^64,
+ * or what flinng_build / flinng_query reject.
  */
 int flinng_build_text(const flinng_params *p, const flinng_text *data,
                       void *stream, flinng_index **out);

@@ -571,6 +571,14 @@ int flinng_query_text(const flinng_index *idx, const flinng_text *q, uint32_t k,
             query_impl(idx, &sets, k, ids, scores, out_on_device, persistent, stream, &tx);
             return;
         }
+        // nothing may be recorded into a graph: it would write the words read back
+        // when another call has them
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) {  // the legacy stream beside a capture
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusNone;
+        }
+        require(cap == hipStreamCaptureStatusNone, "device text cannot be queried under stream capture");
         // the first and last offset are read back while the batch is hashed (which
         // reads no symbol where they decrease)
         ReadbackLease rb(ix);

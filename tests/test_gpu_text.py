@@ -166,3 +166,44 @@ def test_refused_text_leaves_the_outputs_alone(fl, nq):
     want = gi.query_text((sym.cpu().numpy().view(np.uint8), off.cpu().numpy().view(np.uint64)), txt, 10)
     assert np.array_equal(out[0].cpu().numpy().view(np.uint32), want[0])
     assert np.array_equal(out[1].cpu().numpy().view(np.uint32), want[1])
+
+
+@pytest.mark.parametrize("mode", ["thread_local", "relaxed"])
+def test_text_queries_under_capture_are_refused(fl, mode):
+    """Device text is refused under stream capture (the offsets are waited for),
+    before anything is recorded: the graph holds the item-set queries beside it,
+    and text queries and replays do not disturb one another."""
+    import torch
+    data, queries, ex, fam, _, p = _workload("genome")
+    txt = (ex["gram"], ex["radix"], ex["key"])
+    gi = fl.Index(data, fam, p["K"], p["L"], p["R"], p["B"], seed=5, bucket_bits=p["b"])
+    nq = len(ex["queries"][1]) - 1
+    dev = _dev_text(torch, ex["queries"])
+    sets = (torch.from_numpy(queries[0].view(np.int64)).cuda(),
+            torch.from_numpy(queries[1].view(np.int64)).cuda())
+    want = gi.query_text(ex["queries"], txt, 10)
+    new = lambda: (torch.zeros((nq, 10), dtype=torch.int32, device="cuda"),
+                   torch.zeros((nq, 10), dtype=torch.int32, device="cuda"))
+    out, text_out = new(), new()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):  # makes the stream's region
+        gi.query(sets, 10, out=out)
+    torch.cuda.synchronize()
+    log("capture", nq, mode)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s, capture_error_mode=mode):
+        with pytest.raises(fl.FlinngError) as e:
+            gi.query_text(dev, txt, 10, out=text_out)
+        assert e.value.code == fl.EINVAL
+        gi.query(sets, 10, out=out)
+    for i in range(4):
+        for o in out + text_out:
+            o.fill_(-1 - i)
+        torch.cuda.synchronize()
+        graph.replay()
+        gi.query_text(dev, txt, 10, out=text_out)
+        torch.cuda.synchronize()
+        for o in (out, text_out):
+            assert np.array_equal(o[0].cpu().numpy().view(np.uint32), want[0]), i
+            assert np.array_equal(o[1].cpu().numpy().view(np.uint32), want[1]), i
