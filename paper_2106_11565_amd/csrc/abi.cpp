@@ -180,8 +180,7 @@ static void free_index(Index *ix) {
     if (!ix) return;
     (void)hipSetDevice(ix->device);
     (void)hipDeviceSynchronize();  // queries may still be running on any stream
-    for (auto &e : ix->scratch)
-        if (e->ptr) (void)hipFree(e->ptr);
+    for (auto &e : ix->scratch) e->release();
     for (auto &r : ix->readbacks) {
         (void)hipEventDestroy(r.ready);
         (void)hipHostFree(r.host);
@@ -374,12 +373,23 @@ int flinng_index_get_info(const flinng_index *idx, flinng_index_info *info) {
 
 }  // extern "C"
 
-// The index's region for stream s, at least `bytes` long, and its lock (see
-// Index::StreamScratch).  At most 8 streams are remembered; the oldest that no
-// call holds is evicted.
+static void *region_malloc(size_t bytes) {
+    void *p = nullptr;
+    const hipError_t err = hipMalloc(&p, bytes);
+    if (err != hipSuccess) {
+        (void)hipGetLastError();
+        fail(err == hipErrorOutOfMemory ? FLINNG_ENOMEM : FLINNG_EDEVICE,
+             "device allocation of " + std::to_string(bytes) + " bytes failed");
+    }
+    return p;
+}
+
+// The index's region for stream s, its codes at least `bytes` long, with its
+// small piece if asked for, and its lock (see Index::StreamScratch).  At most 8
+// streams are remembered; the oldest that no call holds is evicted.
 using ScratchLock = std::unique_lock<std::mutex>;
 static std::shared_ptr<Index::StreamScratch> lock_scratch(const Index &ix, hipStream_t s, size_t bytes,
-                                                          ScratchLock &lock) {
+                                                          bool small, ScratchLock &lock) {
     std::shared_ptr<Index::StreamScratch> e;
     for (;;) {
         {
@@ -394,8 +404,7 @@ static std::shared_ptr<Index::StreamScratch> lock_scratch(const Index &ix, hipSt
                         ++it;
                         continue;
                     }
-                    if ((*it)->ptr) (void)hipFree((*it)->ptr);
-                    (*it)->ptr = nullptr;
+                    (*it)->release();
                     (*it)->evicted = true;
                     l.unlock();
                     it = ix.scratch.erase(it);
@@ -409,19 +418,13 @@ static std::shared_ptr<Index::StreamScratch> lock_scratch(const Index &ix, hipSt
         if (!e->evicted) break;
         lock.unlock();
     }
+    if (small && !e->small) e->small = region_malloc(SMALL_SCRATCH);
     if (e->cap >= bytes) return e;
     if (e->ptr) (void)hipFree(e->ptr);  // waits for the work using it
     e->ptr = nullptr;
     e->cap = 0;
     const size_t cap = std::max<size_t>(bytes, 64 * 1024);
-    void *p = nullptr;
-    const hipError_t err = hipMalloc(&p, cap);
-    if (err != hipSuccess) {
-        (void)hipGetLastError();
-        fail(err == hipErrorOutOfMemory ? FLINNG_ENOMEM : FLINNG_EDEVICE,
-             "device allocation of " + std::to_string(cap) + " bytes failed");
-    }
-    e->ptr = p;
+    e->ptr = region_malloc(cap);
     e->cap = cap;
     return e;
 }
@@ -469,9 +472,6 @@ struct ReadbackLease {
 
 }  // namespace
 
-// Scratch of a batch that is kept in its stream's region rather than allocated.
-constexpr size_t SMALL_SCRATCH = (size_t)1 << 20;
-
 // check: the offsets of a text batch on the device, on their way to the host;
 // waited for once the hashing is queued, and nothing is written to the outputs
 // of a batch that is refused.
@@ -499,12 +499,14 @@ static void query_impl(const flinng_index *idx, const flinng_input *q, uint32_t 
     const size_t res_bytes = out_on_device ? 0 : Arena::round((size_t)nq * k * 4) * (scores ? 2 : 1);
     const size_t srp_bytes = dense ? srp_scratch_bytes(ix, nq, host_rows ? nullptr : q->values) : 0;
     const bool all = in_bytes + res_bytes + srp_bytes <= SMALL_SCRATCH;
-    Arena a{nullptr, code_bytes + (all ? in_bytes + res_bytes + srp_bytes : 0), 0};
     ScratchLock lock;
-    const auto region = lock_scratch(ix, s, a.cap, lock);
-    a.base = static_cast<char *>(region->ptr);
-    uint32_t *codes = static_cast<uint32_t *>(a.take((size_t)nq * ix.p.L * 4));
-    uint32_t *work = static_cast<uint32_t *>(a.take(4));
+    // (a dense index's regions have the small piece from the first call on, so
+    // that a later call under capture finds it)
+    const auto region = lock_scratch(ix, s, code_bytes, dense || (all && res_bytes > 0), lock);
+    Arena c{static_cast<char *>(region->ptr), code_bytes, 0};
+    Arena a{static_cast<char *>(region->small), SMALL_SCRATCH, 0};
+    uint32_t *codes = static_cast<uint32_t *>(c.take((size_t)nq * ix.p.L * 4));
+    uint32_t *work = static_cast<uint32_t *>(c.take(4));
     if (text) {
         minhash_hash_text(ix, *text, nq, codes, s);
         if (check) {

@@ -109,16 +109,25 @@ struct Index {
     std::vector<uint32_t> gsize_host;     // host copy of gsize
     mutable std::shared_mutex rw;         // query enqueue (shared) / insert swap
     std::mutex insert_mu;                 // one insert at a time
-    // Device scratch of one query batch (its codes above all), one region per
-    // stream the index is queried on: work on one stream runs in order, so a
-    // region is reused without waiting.  Its lock is held while a call queues
-    // the work that uses it (two threads queueing on one stream must not
-    // interleave) and, where its results lie in it, until they are copied out.
-    // Grown (and evicted) with a synchronous free; released with the index.
+    // Device scratch of one query batch, one region for each stream the index is
+    // queried on: work on one stream runs in order, so a region is reused without
+    // waiting.  Its lock is held while a call queues the work that uses it (two
+    // threads queueing on one stream must not interleave) and, where its results
+    // lie in it, until they are copied out.  The codes grow with the batch (with
+    // a synchronous free, as when a region is evicted); a small batch's other
+    // scratch lies apart, in a piece of one size, so that only a batch with more
+    // codes moves the codes of a captured call.  Released with the index.
     struct StreamScratch {
         hipStream_t stream = nullptr;
-        void *ptr = nullptr;
+        void *ptr = nullptr;    // codes
         size_t cap = 0;
+        void *small = nullptr;  // SMALL_SCRATCH bytes, once a call needs them
+        void release() {
+            if (ptr) (void)hipFree(ptr);
+            if (small) (void)hipFree(small);
+            ptr = small = nullptr;
+            cap = 0;
+        }
         bool evicted = false;
         std::mutex mu;
     };
@@ -134,6 +143,9 @@ struct Index {
     mutable std::vector<Readback> readbacks;  // the free ones
     bool counted = false;                 // among its device's live indexes
 };
+
+// Scratch of a batch that is kept in its stream's region rather than allocated.
+constexpr size_t SMALL_SCRATCH = (size_t)1 << 20;
 
 inline uint64_t nbuckets(const Index &ix) { return 1ull << ix.nbits; }
 // Bytes allocated for n list entries of csz bytes: rounded up to 16 bytes

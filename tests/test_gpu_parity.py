@@ -506,3 +506,38 @@ def test_one_query_kernel_register_budgets(fl, B):
         want = oracle_query(oi, Q, k)
         got = gi.query(Q, k)
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), k
+
+
+@pytest.mark.parametrize("family", [0, 1])
+def test_small_batches_leave_a_captured_call_alone(fl, family):
+    """A captured query keeps its scratch while the program goes on with calls on
+    the same stream whose codes are fewer but whose rows and results, staged
+    there, take more room."""
+    import torch
+    X, Q, _ = (synth.dense_gmm if family == 0 else synth.dense_relu)(N=3000, d=512, n_centres=30, nq=200)
+    gi, oi = build_both(fl, family, X, 8, 6, 3, 30, 23)
+    want = oracle_query(oi, Q, 20)
+    nq = 60
+    dev = torch.from_numpy(np.ascontiguousarray(Q[:nq]).view(np.int16 if family else np.float32)).cuda()
+    out = (torch.zeros((nq, 20), dtype=torch.int32, device="cuda"),
+           torch.zeros((nq, 20), dtype=torch.int32, device="cuda"))
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        gi.query(dev, 20, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        gi.query(dev, 20, out=out)
+    for i, n in enumerate((1, 50, 100, 200, 3)):
+        log("captured call", family, "beside", n)
+        with torch.cuda.stream(s):
+            got = gi.query(Q[:n], 20)
+        assert np.array_equal(got[0], want[0][:n]) and np.array_equal(got[1], want[1][:n])
+        for o in out:
+            o.fill_(-1 - i)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out[0].cpu().numpy().view(np.uint32), want[0][:nq]), n
+        assert np.array_equal(out[1].cpu().numpy().view(np.uint32), want[1][:nq]), n
