@@ -266,9 +266,11 @@ int flinng_query_noalloc(const flinng_index *idx, const flinng_input *q, uint32_
  * each other.  The point's cell then enters the reverse-index list of its
  * bucket in every table (lists stay deduplicated sets, members ascending).
  * New arrays are built beside the old ones (the index's memory transiently
- * doubles) and swapped in while no query is being enqueued: queries and
- * served batches in flight or queued see the index either before or after
- * the insert, never a mix.  The call synchronizes the device.  One insert
+ * doubles; beside it the arrivals' own lists, about R*L entries of 16 bytes per
+ * point, up to 1 GiB of bucket offsets, or one table's, and up to 6 GiB of
+ * sorting scratch) and swapped in while no query is being enqueued: queries and
+ * served batches in flight or queued see the index either before or after the
+ * insert, never a mix.  The call synchronizes the device.  One insert
  * runs at a time per index; FLINNG_EINVAL past 2^32 - 2 points.
  */
 int flinng_index_insert(flinng_index *idx, const flinng_input *data, void *stream);

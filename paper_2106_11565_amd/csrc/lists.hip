@@ -460,18 +460,19 @@ __global__ void added_cells_kernel(const uint32_t *__restrict__ doff, const Cell
 }
 
 // The added cells packed: cell, and the new position of each (the old entries
-// before it plus the added ones).  rank: exclusive prefix of `add`.
+// before it plus the added ones).  rank: prefix of `add`, from `base` (the cells
+// added to the tables before) to *nadd.
 template <typename CellT>
 __global__ void pack_added_kernel(const CellT *__restrict__ dcells, const uint32_t *__restrict__ before,
-                                  const uint32_t *__restrict__ rank, uint64_t n,
+                                  const uint32_t *__restrict__ rank, uint64_t n, uint64_t base,
                                   const uint64_t *__restrict__ nadd, uint32_t *__restrict__ at,
                                   CellT *__restrict__ ac) {
     const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     const uint32_t r = rank[e], nx = e + 1 < n ? rank[e + 1] : (uint32_t)*nadd;
     if (nx == r) return;
-    at[r] = before[e] + r;
-    ac[r] = dcells[e];
+    at[r - (uint32_t)base] = before[e] + r;
+    ac[r - (uint32_t)base] = dcells[e];
 }
 
 // How many of the ascending values v[0, n) lie below x.
@@ -484,19 +485,21 @@ __device__ inline uint64_t count_below(const uint32_t *__restrict__ v, uint64_t 
     return lo;
 }
 
-// New entry p is the a-th added cell where at[a] = p, else old entry p minus
-// the added cells before it.  A workgroup writes 2048 consecutive entries: the
-// first of its added cells by one binary search, the rest counted from them.
+// New entries [first, end), those of some tables: entry p is the a-th added cell
+// where at[a] = p, else old entry p minus the added cells before it (`base` of
+// them in earlier tables).  A workgroup writes 2048 consecutive entries: the first
+// of its added cells by one binary search, the rest counted from them.
 constexpr uint32_t MG_TILE = 2048;
 template <typename CellT>
 __global__ __launch_bounds__(256) void merge_cells_kernel(const CellT *__restrict__ ocells,
                                                           const uint32_t *__restrict__ at,
                                                           const CellT *__restrict__ ac, uint64_t nadd,
-                                                          uint64_t total, CellT *__restrict__ out) {
+                                                          uint64_t base, uint64_t first, uint64_t end,
+                                                          CellT *__restrict__ out) {
     __shared__ uint64_t range[2];
     __shared__ uint32_t sat[MG_TILE];
-    const uint64_t p0 = (uint64_t)blockIdx.x * MG_TILE;
-    const uint64_t p1 = p0 + MG_TILE < total ? p0 + MG_TILE : total;
+    const uint64_t p0 = first + (uint64_t)blockIdx.x * MG_TILE;
+    const uint64_t p1 = p0 + MG_TILE < end ? p0 + MG_TILE : end;
     if (threadIdx.x < 2) range[threadIdx.x] = count_below(at, nadd, threadIdx.x ? p1 : p0);
     __syncthreads();
     const uint64_t a0 = range[0];
@@ -509,11 +512,12 @@ __global__ __launch_bounds__(256) void merge_cells_kernel(const CellT *__restric
             const uint32_t m = (lo + hi) / 2;
             if (sat[m] < p) lo = m + 1; else hi = m;
         }
-        out[p] = (lo < na && sat[lo] == p) ? ac[a0 + lo] : ocells[p - (a0 + lo)];
+        out[p] = (lo < na && sat[lo] == p) ? ac[a0 + lo] : ocells[p - (base + a0 + lo)];
     }
 }
 
-// New offset = old offset + the added cells of all earlier lists.
+// New offset = old offset + the added cells of all earlier lists (rank counts
+// those of the tables before too).
 __global__ void merge_offsets_kernel(const uint32_t *__restrict__ ooff,
                                      const uint32_t *__restrict__ doff,
                                      const uint32_t *__restrict__ rank, uint64_t nd,
@@ -622,9 +626,10 @@ constexpr uint64_t LISTS_SCRATCH = 6ull << 30;
 // keeps both sides of a pass in the 256 MB last-level cache
 constexpr uint64_t SORT_TMP = 96ull << 20;
 
-Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, uint64_t n,
-                 hipStream_t s) {
-    const uint32_t L = ix.p.L;
+// The lists of tables tb .. tb+L-1; their offsets ([L][nbuckets + 1]) go to
+// `off`, the entries counted from the first.
+static Lists make_tables(const Index &ix, const uint32_t *codes, const uint16_t *grp, uint64_t n,
+                         uint32_t tb, uint32_t L, uint32_t *off, hipStream_t s) {
     const uint64_t nbk = nbuckets(ix);
     const size_t csz = ix.cell_bytes;
     const uint64_t per_table = 8 * n + 4 * n + 8 * (n / (RUN_SHORT + 1) + 2);
@@ -633,7 +638,6 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
     const uint64_t nblk = (nbk + 1 + n + OB_BLOCK - 1) / OB_BLOCK;
 
     Lists out;
-    HipMem offsets = hip_mem((size_t)L * (nbk + 1) * 4, s);
     std::vector<std::pair<HipMem, uint64_t>> parts;  // the batches' cells
     Pieces pc;
     auto piece = [&](size_t bytes) { return pc.add(bytes); };
@@ -658,7 +662,7 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
         const uint32_t nt = std::min(bt, L - t0);
         // codes by table (in the counts' place), sorted points
         hipLaunchKernelGGL(transpose_codes_kernel, dim3(blocks_for(n, TR_P), blocks_for(nt, TR_T)),
-                           dim3(256), 0, s, codes, n, L, t0, nt, b.pos);
+                           dim3(256), 0, s, codes, n, ix.p.L, tb + t0, nt, b.pos);
         FL_CHECK_LAUNCH();
         for (uint32_t q = 0; q < nt; q += stn)
             pair_sort(b.pos + (uint64_t)q * n, n, std::min(stn, nt - q), (int)ix.nbits,
@@ -680,7 +684,7 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
         FL_CHECK_LAUNCH();
         hipLaunchKernelGGL(bucket_offsets_kernel, dim3((unsigned)nblk, nt), dim3(256), 0, s, b.pairs,
                            b.pos, n, nbk, b.blo, nblk, b.tstart,
-                           static_cast<uint32_t *>(offsets.get()) + (uint64_t)t0 * (nbk + 1));
+                           off + (uint64_t)t0 * (nbk + 1));
         FL_CHECK_LAUNCH();
         FL_HIP(hipStreamSynchronize(s));
         const uint64_t total = got[0];
@@ -707,75 +711,123 @@ Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, ui
         parts.clear();
         parts.emplace_back(std::move(all), out.entries);
     }
-    out.offsets = static_cast<uint32_t *>(offsets.release());
     out.cells = parts[0].first.release();
     return out;
 }
 
+Lists make_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp, uint64_t n,
+                 hipStream_t s) {
+    HipMem offsets = hip_mem((size_t)ix.p.L * (nbuckets(ix) + 1) * 4, s);
+    Lists out = make_tables(ix, codes, grp, n, 0, ix.p.L, static_cast<uint32_t *>(offsets.get()), s);
+    out.offsets = static_cast<uint32_t *>(offsets.release());
+    return out;
+}
+
+// Offsets of the arrivals' own lists, at most this much for more than one table:
+// an insert works through the tables in batches, so that what it needs beside the
+// new version stays bounded where the offsets are most of an index (255 tables of
+// 2^24 buckets: 17 GB of them).  The workloads' indexes take one batch (URL
+// strings, 48 tables of 2^22: 0.8 GB).
+constexpr uint64_t MERGE_OFFSETS = 1ull << 30;
+
 namespace {
 
+// The cells that the arrivals add to a batch of tables.
+struct Added {
+    HipMem list;            // the arrivals' own cells
+    DevBuf ws;
+    uint32_t *at = nullptr; // new position of each
+    void *cells = nullptr;
+    uint64_t n = 0;
+    uint64_t before = 0;    // cells added to the tables before
+    uint64_t first = 0;     // old entries of the tables before
+};
+
+// Tables tb .. tb+nt-1: the new offsets from the old ones, and the cells to add.
 template <typename CellT>
-void merge_into(const Index &ix, Lists &d, Lists &out, hipStream_t s) {
-    const uint64_t nbk = nbuckets(ix), no = (uint64_t)ix.p.L * (nbk + 1), nd = d.entries;
+Added merge_tables(const Index &ix, const uint32_t *codes, const uint16_t *grp_rows, uint64_t n,
+                   uint32_t tb, uint32_t nt, uint64_t before, uint32_t *doff, HipMem &offsets,
+                   hipStream_t s) {
+    const uint64_t nbk = nbuckets(ix), no = (uint64_t)nt * (nbk + 1);
+    const Lists d = make_tables(ix, codes, grp_rows, n, tb, nt, doff, s);
+    Added out;
+    out.list.reset(d.cells);
+    out.before = before;
+    const uint64_t nd = d.entries;  // every point has a cell in every table
     const CellT *dc = static_cast<const CellT *>(d.cells);
     const CellT *oc = static_cast<const CellT *>(ix.cells);
+    const uint32_t *ooff = ix.offsets + (uint64_t)tb * (nbk + 1);
     Pieces pc;
-    const size_t o_rank = pc.add((nd + 1) * 4), o_before = pc.add((nd + 1) * 4), o_at = pc.add((nd + 1) * 4),
-                 o_ac = pc.add((nd + 1) * sizeof(CellT)), o_total = pc.add(8),
+    const size_t o_rank = pc.add(nd * 4), o_below = pc.add(nd * 4), o_at = pc.add(nd * 4),
+                 o_ac = pc.add(nd * sizeof(CellT)), o_total = pc.add(8),
                  o_sc = pc.add(scan_scratch_bytes(nd));
-    DevBuf ws = DevBuf::pooled(pc.total, s);
-    char *w = ws.as<char>();
-    uint32_t *rk = reinterpret_cast<uint32_t *>(w + o_rank), *before = reinterpret_cast<uint32_t *>(w + o_before);
-    uint32_t *at = reinterpret_cast<uint32_t *>(w + o_at);
-    CellT *ac = reinterpret_cast<CellT *>(w + o_ac);
+    out.ws = DevBuf::pooled(pc.total, s);
+    char *w = out.ws.as<char>();
+    uint32_t *rk = reinterpret_cast<uint32_t *>(w + o_rank), *below = reinterpret_cast<uint32_t *>(w + o_below);
+    out.at = reinterpret_cast<uint32_t *>(w + o_at);
+    out.cells = w + o_ac;
     uint64_t *total = reinterpret_cast<uint64_t *>(w + o_total);
-    if (nd) {
-        hipLaunchKernelGGL(added_cells_kernel<CellT>, dim3(blocks_for(nd, 256)), dim3(256), 0, s,
-                           d.offsets, dc, nd, ix.offsets, oc, ix.p.L, nbk, rk, before);
-        FL_CHECK_LAUNCH();
-    }
-    device_exclusive_scan_u32(rk, nd, 0, total, w + o_sc, s);
-    if (nd) {
-        hipLaunchKernelGGL(pack_added_kernel<CellT>, dim3(blocks_for(nd, 256)), dim3(256), 0, s, dc,
-                           before, rk, nd, total, at,
-                           ac);
-        FL_CHECK_LAUNCH();
-    }
-    uint64_t nadd = 0;
-    FL_HIP(hipMemcpyAsync(&nadd, total, 8, hipMemcpyDeviceToHost, s));
-    out.offsets = static_cast<uint32_t *>(pool_malloc(no * 4, s));
-    hipLaunchKernelGGL(merge_offsets_kernel, dim3(blocks_for(no, 256)), dim3(256), 0, s, ix.offsets,
-                       d.offsets, rk, nd, total, no, out.offsets);
+    hipLaunchKernelGGL(added_cells_kernel<CellT>, dim3(blocks_for(nd, 256)), dim3(256), 0, s, doff, dc, nd,
+                       ooff, oc, nt, nbk, rk, below);
+    FL_CHECK_LAUNCH();
+    device_exclusive_scan_u32(rk, nd, before, total, w + o_sc, s);
+    hipLaunchKernelGGL(pack_added_kernel<CellT>, dim3(blocks_for(nd, 256)), dim3(256), 0, s, dc, below, rk,
+                       nd, before, total, out.at, static_cast<CellT *>(out.cells));
+    FL_CHECK_LAUNCH();
+    uint64_t after = 0;
+    uint32_t first = 0;
+    FL_HIP(hipMemcpyAsync(&after, total, 8, hipMemcpyDeviceToHost, s));
+    if (tb) FL_HIP(hipMemcpyAsync(&first, ooff, 4, hipMemcpyDeviceToHost, s));
+    if (!offsets) offsets = hip_mem(ix.p.L * (nbk + 1) * 4, s);
+    hipLaunchKernelGGL(merge_offsets_kernel, dim3(blocks_for(no, 256)), dim3(256), 0, s, ooff, doff, rk, nd,
+                       total, no, static_cast<uint32_t *>(offsets.get()) + (uint64_t)tb * (nbk + 1));
     FL_CHECK_LAUNCH();
     FL_HIP(hipStreamSynchronize(s));
+    out.n = after - before;
+    out.first = first;
+    return out;
+}
+
+template <typename CellT>
+Lists merge_into(const Index &ix, const uint32_t *codes, const uint16_t *grp_rows, uint64_t n,
+                 hipStream_t s) {
+    const uint32_t L = ix.p.L;
+    const uint64_t row = nbuckets(ix) + 1;
+    const uint32_t bt = (uint32_t)std::min<uint64_t>(L, std::max<uint64_t>(1, MERGE_OFFSETS / (row * 4)));
+    std::vector<Added> added;
+    uint64_t nadd = 0;
+    HipMem doff = hip_mem(bt * row * 4, s);  // of one batch at a time
+    HipMem offsets;
+    for (uint32_t tb = 0; tb < L; tb += bt) {
+        added.push_back(merge_tables<CellT>(ix, codes, grp_rows, n, tb, std::min(bt, L - tb), nadd,
+                                            static_cast<uint32_t *>(doff.get()), offsets, s));
+        nadd += added.back().n;
+    }
+    Lists out;
     out.entries = ix.list_entries + nadd;
     if (out.entries > 0xFFFFFFFFull) fail(FLINNG_EINVAL, "reverse index exceeds 2^32 entries");
     HipMem cells = cells_with_tail(out.entries, sizeof(CellT), s);
-    if (out.entries) {
-        hipLaunchKernelGGL(merge_cells_kernel<CellT>, dim3(blocks_for(out.entries, MG_TILE)), dim3(256),
-                           0, s, oc, at, ac, nadd, out.entries,
-                           static_cast<CellT *>(cells.get()));
+    for (size_t i = 0; i < added.size(); ++i) {
+        const Added &a = added[i];
+        const uint64_t p0 = a.first + a.before;
+        const uint64_t p1 = i + 1 < added.size() ? added[i + 1].first + added[i + 1].before : out.entries;
+        hipLaunchKernelGGL(merge_cells_kernel<CellT>, dim3(blocks_for(p1 - p0, MG_TILE)), dim3(256), 0, s,
+                           static_cast<const CellT *>(ix.cells), a.at, static_cast<const CellT *>(a.cells),
+                           a.n, a.before, p0, p1, static_cast<CellT *>(cells.get()));
         FL_CHECK_LAUNCH();
     }
     FL_HIP(hipStreamSynchronize(s));
+    out.offsets = static_cast<uint32_t *>(offsets.release());
     out.cells = cells.release();
+    return out;
 }
 
 }  // namespace
 
 Lists merge_lists(const Index &ix, const uint32_t *codes, const uint16_t *grp_rows, uint64_t n,
                   hipStream_t s) {
-    Lists d = make_lists(ix, codes, grp_rows, n, s), out;
-    try {
-        if (ix.cell_bytes == 2) merge_into<uint16_t>(ix, d, out, s);
-        else merge_into<uint32_t>(ix, d, out, s);
-    } catch (...) {
-        free_lists(d);
-        free_lists(out);
-        throw;
-    }
-    free_lists(d);
-    return out;
+    return ix.cell_bytes == 2 ? merge_into<uint16_t>(ix, codes, grp_rows, n, s)
+                              : merge_into<uint32_t>(ix, codes, grp_rows, n, s);
 }
 
 }  // namespace flinng

@@ -155,3 +155,57 @@ def test_insert_while_serving(fl):
         assert max(v) >= lo
         lo = max(lo, min(v))
     log("served", len(seen), "requests across", len(versions), "index versions")
+
+
+def test_insert_memory_is_bounded_where_offsets_dominate(fl):
+    """An index of 128 tables of 2^24 buckets (8.6 GB of offsets): an insert
+    needs room for one new copy of them and a bounded part more."""
+    import torch
+    n, L = 3000, 128
+    vals = (np.arange(n, dtype=np.uint64) * 2654435761 % 2**32).astype(np.uint32)
+    sets = lambda a, b: (vals[a:b], np.arange(b - a + 1, dtype=np.uint64))
+    gi = fl.Index(sets(0, n - 100), fl.MINHASH_U32, 1, L, 4, 1000, seed=3, bucket_bits=24)
+    offsets = L * (2**24 + 1) * 4
+    free0 = torch.cuda.mem_get_info()[0]
+    low, stop = [free0], threading.Event()
+
+    def watch():
+        while not stop.is_set():
+            low[0] = min(low[0], torch.cuda.mem_get_info()[0])
+
+    th = threading.Thread(target=watch)
+    th.start()
+    try:
+        gi.insert(sets(n - 100, n))
+    finally:
+        stop.set()
+        th.join()
+    log("insert", "offsets", offsets, "taken", free0 - low[0])
+    assert free0 - low[0] < offsets + (5 << 29)
+    ids, sc = gi.query(sets(0, n), 1)
+    assert np.array_equal(ids[:, 0], np.arange(n)) and np.all(sc == L)
+
+
+def test_insert_in_batches_of_tables(fl):
+    """20 tables of 2^24 buckets: the arrivals' lists are made and merged 15
+    tables at a time; the lists against the definition."""
+    n, L, R, B = 4000, 20, 3, 10
+    rng = np.random.default_rng(5)
+    vals = rng.integers(0, 900, n).astype(np.uint64) * 2654435761 % 2**32
+    sets = lambda a, b: (vals[a:b].astype(np.uint32), np.arange(b - a + 1, dtype=np.uint64))
+    gi = fl.Index(sets(0, 2500), fl.MINHASH_U32, 1, L, R, B, seed=11, bucket_bits=24)
+    gi.insert(sets(2500, 2501))
+    gi.insert(sets(2501, n))
+    offs, cells, groups = gi.export()
+    codes = gi.debug_hash(sets(0, n)).astype(np.int64)
+    assert offs[0, 0] == 0 and offs[-1, -1] == len(cells)
+    assert np.array_equal(offs[1:, 0], offs[:-1, -1])
+    for t in range(L):
+        key = codes[:, t][None, :] * 64 + np.arange(R)[:, None] * B + groups
+        want = np.unique(key)
+        lo, hi = int(offs[t, 0]), int(offs[t, -1])
+        assert np.array_equal(cells[lo:hi], want % 64), t
+        assert np.all(np.diff(offs[t].astype(np.int64)) >= 0)
+        b = np.unique(want // 64)
+        assert np.array_equal(offs[t, b] - lo, np.searchsorted(want // 64, b)), t
+        assert np.array_equal(offs[t, b + 1] - lo, np.searchsorted(want // 64, b, side="right")), t
