@@ -195,12 +195,13 @@ __global__ void prep_kernel(const void *__restrict__ xin, uint64_t n, uint32_t d
 // consecutive k values at 8*(l/16) of each 32-wide k step, identically for
 // X and W, so every product pairs x[row][k] with w[col][k].
 // Output of a 16x16 tile: lane l holds rows 4*(l/16)+i, column l%16.
-// Bound by the latency of its loads (a few workgroups per compute unit at
-// most): two sets of fragments, so the 16 loads of the next 32 k are in flight
-// during the 48 products of these.  With one set the compiler waited for each
-// fragment in turn before its four products; a whole query call on 4,096 rows
-// of d = 768 went from 254 to 230 us.  The order of the products is unchanged.
-template <int MR, int NR, int WM, int WN, int NSPLIT>
+// Bound by the latency of its loads.  SETS = 2: two sets of fragments, so the 16
+// loads of the next 32 k are in flight during the 48 products of these, but one
+// wavefront per SIMD (269 registers); with one set the compiler waits for each
+// fragment in turn before its four products, and two share a SIMD.  A whole query
+// call on 4,096 rows of d = 768 went from 254 to 230 us with two.  The order of
+// the products is the same.
+template <int MR, int NR, int WM, int WN, int NSPLIT, int SETS>
 __global__ __launch_bounds__(64 * WM * WN) void srp_mfma_kernel(
     const uint16_t *__restrict__ planes, uint64_t plane_stride, uint32_t ld,
     const uint16_t *__restrict__ w, uint32_t dpad, const float *__restrict__ nx,
@@ -237,41 +238,57 @@ __global__ __launch_bounds__(64 * WM * WN) void srp_mfma_kernel(
         pb[b] = w + (uint64_t)c * dpad + lk;
     }
 
-    // the fragments of the next 32 k are loaded before this step's products
-    // (the last step loads its own again; nothing reads them)
-    uint4 fb[2][NR], fa[2][NSPLIT][MR];
-    auto fetch = [&](uint32_t k0, uint4(&xb)[NR], uint4(&xa)[NSPLIT][MR]) {
+    auto load = [](const uint16_t *p) { return *reinterpret_cast<const uint4 *>(p); };
+    auto product = [&](const uint4(&xb)[NR], const uint4(&xa)[MR]) {
 #pragma unroll
-        for (int b = 0; b < NR; ++b) xb[b] = *reinterpret_cast<const uint4 *>(pb[b] + k0);
+        for (int a = 0; a < MR; ++a)
 #pragma unroll
-        for (int sp = 0; sp < NSPLIT; ++sp)
-#pragma unroll
-            for (int a = 0; a < MR; ++a)
-                xa[sp][a] = *reinterpret_cast<const uint4 *>(pa[a] + sp * plane_stride + k0);
+            for (int b = 0; b < NR; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, xa[a]), __builtin_bit_cast(bf16x8, xb[b]), acc[a][b], 0, 0, 0);
     };
-    auto product = [&](const uint4(&xb)[NR], const uint4(&xa)[NSPLIT][MR]) {
+    if constexpr (SETS == 1) {
+        for (uint32_t k0 = 0; k0 < dpad; k0 += 32) {
+            uint4 fb[NR];
 #pragma unroll
-        for (int sp = 0; sp < NSPLIT; ++sp)
+            for (int b = 0; b < NR; ++b) fb[b] = load(pb[b] + k0);
 #pragma unroll
-            for (int a = 0; a < MR; ++a)
+            for (int sp = 0; sp < NSPLIT; ++sp) {
+                uint4 fa[MR];
 #pragma unroll
-                for (int b = 0; b < NR; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, xa[sp][a]), __builtin_bit_cast(bf16x8, xb[b]),
-                        acc[a][b], 0, 0, 0);
-    };
-    fetch(0, fb[0], fa[0]);
-    for (uint32_t k0 = 0; k0 + 64 <= dpad; k0 += 64) {
-        fetch(k0 + 32, fb[1], fa[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        product(fb[0], fa[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(k0 + 64 < dpad ? k0 + 64 : k0, fb[0], fa[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        product(fb[1], fa[1]);
-        __builtin_amdgcn_sched_barrier(0);
+                for (int a = 0; a < MR; ++a) fa[a] = load(pa[a] + sp * plane_stride + k0);
+                product(fb, fa);
+            }
+        }
+    } else {
+        // the fragments of the next 32 k are loaded before this step's products
+        // (the last step loads its own again; nothing reads them)
+        uint4 fb[2][NR], fa[2][NSPLIT][MR];
+        auto fetch = [&](uint32_t k0, uint4(&xb)[NR], uint4(&xa)[NSPLIT][MR]) {
+#pragma unroll
+            for (int b = 0; b < NR; ++b) xb[b] = load(pb[b] + k0);
+#pragma unroll
+            for (int sp = 0; sp < NSPLIT; ++sp)
+#pragma unroll
+                for (int a = 0; a < MR; ++a) xa[sp][a] = load(pa[a] + sp * plane_stride + k0);
+        };
+        auto step = [&](const uint4(&xb)[NR], const uint4(&xa)[NSPLIT][MR]) {
+#pragma unroll
+            for (int sp = 0; sp < NSPLIT; ++sp) product(xb, xa[sp]);
+        };
+        fetch(0, fb[0], fa[0]);
+        for (uint32_t k0 = 0; k0 + 64 <= dpad; k0 += 64) {
+            fetch(k0 + 32, fb[1], fa[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            step(fb[0], fa[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(k0 + 64 < dpad ? k0 + 64 : k0, fb[0], fa[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            step(fb[1], fa[1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (dpad % 64) step(fb[0], fa[0]);
     }
-    if (dpad % 64) product(fb[0], fa[0]);
 
     // Epilogue: trusted sign bits and flags, 16 columns per ballot group.
     unsigned long long flagged = 0;
@@ -1091,6 +1108,20 @@ size_t srp_scratch_bytes(const Index &ix, uint64_t n, const void *xdev) {
            2 * Arena::round(n * Hw * 4) + Arena::round(16);
 }
 
+// Whether srp_mfma_kernel takes two sets of fragments: where every wavefront (a
+// tile of 64 rows and 64 hyperplanes) has a SIMD of its own, and for longer rows.
+// Short rows have few loads to hide, and one to four rounds of wavefronts leave
+// the last one part empty.  Hash stage, one set against two: 100,000 rows, 768
+// hyperplanes, d = 64 397 and 523 us, 256 875 and 908, 300 1060 and 1010, 768
+// 2,200 and 1,920; 20,000 rows, 256 hyperplanes (1,252 tiles), d = 300 152 and 171,
+// 512 188 and 204, 768 291 and 279; 64 hyperplanes leave half of a workgroup out:
+// 100,000 rows, d = 300 350 and 332.
+static bool two_sets(uint64_t n, uint32_t H, uint32_t d) {
+    const uint64_t tiles = (n + 63) / 64 * ((H + 63) / 64);
+    if (tiles <= 1024) return true;
+    return d >= (tiles < 4096 && H > 64 ? 640u : 288u);
+}
+
 void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipStream_t s,
               unsigned long long *ctr, Arena *ws, float *proj_dev) {
     const uint64_t n = in.count;
@@ -1154,11 +1185,15 @@ void srp_hash(const Index &ix, const flinng_input &in, uint32_t *codes_dev, hipS
     if (!ctr) ctr = own;
     dim3 grid((H + 16 * NR * WN - 1) / (16 * NR * WN),
               (unsigned)((n + 16 * MR * WM - 1) / (16 * MR * WM)));
-    hipLaunchKernelGGL((srp_mfma_kernel<MR, NR, WM, WN, 3>), grid, dim3(64 * WM * WN), 0, s,
-                       planes, (uint64_t)n * dpad, dpad, ix.hyp, dpad, nx, ix.hypnorm, n, H, Hw,
-                       gamma, tau_abs, reinterpret_cast<uint16_t *>(bits),
-                       reinterpret_cast<uint16_t *>(flags), ctr, proj_dev);
-    FL_CHECK_LAUNCH();
+    auto project = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(64 * WM * WN), 0, s, planes, (uint64_t)n * dpad, dpad, ix.hyp,
+                           dpad, nx, ix.hypnorm, n, H, Hw, gamma, tau_abs,
+                           reinterpret_cast<uint16_t *>(bits), reinterpret_cast<uint16_t *>(flags), ctr,
+                           proj_dev);
+        FL_CHECK_LAUNCH();
+    };
+    if (two_sets(n, H, d)) project(srp_mfma_kernel<MR, NR, WM, WN, 3, 2>);
+    else project(srp_mfma_kernel<MR, NR, WM, WN, 3, 1>);
     hipLaunchKernelGGL(srp_recheck_pack_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256),
                        4 * Hw * sizeof(uint32_t), s, static_cast<const float *>(xdev), n, d, ix.hyp, dpad, bits, flags, Hw,
                        H, K, L, codes_dev, ctr + 1);

@@ -35,3 +35,21 @@ def test_large_batch_codes_equal_oracle(fl, n, d, K, L):
     got = gi.debug_hash(X)
     assert np.array_equal(got, want)
     assert np.array_equal(gi.debug_hash(X[:100]), want[:100])
+
+
+@pytest.mark.parametrize("n,d,K,L", [
+    (65536, 33, 6, 5),    # 1,024 tiles: two sets of fragments
+    (65537, 33, 6, 5),    # one more: one set, an odd count of 32-wide steps
+    (65537, 288, 3, 5),   # two sets again, an odd count of steps
+    (33000, 100, 13, 5),  # 1,032 tiles of two columns of workgroups, one set
+    (33000, 640, 13, 5),  # two sets
+])
+def test_fp32_fragment_sets_equal_oracle(fl, n, d, K, L):
+    """fp32 rows on both sides of the rule that picks one or two sets of operand
+    fragments."""
+    rng = np.random.default_rng(n + d)
+    log("fp32 fragments", n, d, K * L)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    gi = fl.Index(x[:500], 0, K, L, 2, 50, seed=99)
+    w = oracle.hyperplanes(99, K * L, d)
+    assert np.array_equal(gi.debug_hash(x), oracle.srp_codes(x.astype(np.float64), 99, K, L, w=w))
