@@ -12,8 +12,9 @@
 // Mapping: one wavefront per set.  The set's items are staged in LDS 128 at a
 // time; every lane owns one hash function at a time and takes its minimum over
 // the staged items (a broadcast read per item).  The last L*K mod 64 functions
-// share the lanes as floor(64 / that) slices of the items each, combined by LDS
-// minima.  Sets may also be given as text: the items of an n-gram set are then
+// share the lanes as floor(64 / that) slices of the items each, or in several
+// passes where that leaves fewer lanes idle, combined by LDS minima.  Small sets
+// and few functions read the items themselves.  Sets may also be given as text: the items of an n-gram set are then
 // made from the staged symbols in the wavefront itself and never stored.
 //
 // What bounds it: vector instructions.  On gfx950 a 32-bit multiply issues like
@@ -93,12 +94,23 @@ constexpr uint32_t MH_CHUNK = 128;           // items staged at a time
 constexpr uint32_t MH_BUF = MH_CHUNK + 64;   // padded with copies of the last for the slices
 constexpr uint32_t MH_SYMS = MH_CHUNK + 64;  // symbols of a chunk's windows (n-grams of up to 64)
 
-template <typename ItemT, bool TEXT>
-__global__ __launch_bounds__(256) void minhash_kernel(const ItemT *__restrict__ items,
+// Sets are not staged where it is not worth it: up to this many functions, or up to
+// 16 items a slice (8 for one slice).  20,000 sets of 64-bit items, staged and not:
+// 4 functions, 81 items 22.7 and 18.1 us; 12 functions, 4 items 16.4 and 13.6, 40
+// items 22.9 and 20.3, 300 items 63.5 and 74; 31 functions, 81 items 44 and 47.
+constexpr uint32_t MH_FEW_FUNCTIONS = 8;
+// Items up to which the last functions are taken in one pass.
+constexpr uint32_t MH_FEW_ITEMS = 32;
+
+// MANY: the last LK mod 64 functions in several passes (`slices` of the items each)
+// for sets of more than MH_FEW_ITEMS.
+// (the wavefronts per SIMD are those that the registers of one pass allow)
+template <typename ItemT, bool TEXT, bool MANY>
+__global__ __launch_bounds__(256, TEXT ? (sizeof(ItemT) == 4 ? 7 : 6) : 8) void minhash_kernel(const ItemT *__restrict__ items,
                                                       const uint64_t *__restrict__ offsets,
                                                       TextSource tx, uint64_t nsets, uint32_t K,
                                                       uint32_t L, uint32_t bbits, uint64_t key,
-                                                      uint32_t *__restrict__ codes) {
+                                                      uint32_t slices, uint32_t *__restrict__ codes) {
     extern __shared__ uint32_t lds32[];
     const int lane = threadIdx.x % 64;
     const int wave = threadIdx.x / 64;
@@ -125,8 +137,25 @@ __global__ __launch_bounds__(256) void minhash_kernel(const ItemT *__restrict__ 
         n = n >= tx.gram ? n - tx.gram + 1 : 0;
     }
     // the last LK mod 64 functions: S slices of the items each
-    const uint32_t full = LK & ~63u, rem = LK - full, S = rem ? 64 / rem : 1;
+    const uint32_t full = LK & ~63u, rem = LK - full;
+    const bool many = MANY && n > MH_FEW_ITEMS;
+    const uint32_t S = many ? slices : rem ? 64 / rem : 1;
     const uint32_t rf = (uint32_t)lane / S, rs = (uint32_t)lane - rf * S;
+    if (!TEXT && LK <= 64 && (LK <= MH_FEW_FUNCTIONS || n <= (S > 1 ? 16 * S : 8)) && !many) {
+        // each lane reads its items itself
+        lds_fence();
+        if (rf < LK) {
+            const HashFn<ItemT> h(sm64(key, rf));
+            uint32_t mn = 0xFFFFFFFFu;
+            for (const ItemT *p = items + beg + rs, *e = items + beg + n; p < e; p += S) {
+                uint32_t v = h(*p);
+                v ^= v >> 31;
+                mn = v < mn ? v : mn;
+            }
+            atomicMin(&mins[rf], mn);
+        }
+        n = 0;
+    }
     for (uint64_t c0 = 0; c0 < n; c0 += MH_CHUNK) {
         const uint32_t m = (uint32_t)(n - c0 < MH_CHUNK ? n - c0 : MH_CHUNK);
         lds_fence();  // the last chunk's reads are done
@@ -168,11 +197,27 @@ __global__ __launch_bounds__(256) void minhash_kernel(const ItemT *__restrict__ 
             return mn;
         };
         for (uint32_t f0 = 0; f0 < full; f0 += 64) {
-            const uint32_t mn = minimum(f0 + lane, 0, 1);
+            uint32_t mn = 0xFFFFFFFFu;
+            if (m <= 12) {  // some lane's minimum nearly always has the top bit
+                const HashFn<ItemT> h(sm64(key, f0 + lane));
+                for (uint32_t i = 0; i < m; ++i) {
+                    uint32_t v = h(buf[i]);
+                    v ^= v >> 31;
+                    mn = v < mn ? v : mn;
+                }
+            } else {
+                mn = minimum(f0 + lane, 0, 1);
+            }
             const uint32_t old = mins[f0 + lane];
             mins[f0 + lane] = mn < old ? mn : old;
         }
-        if (rf < rem) atomicMin(&mins[full + rf], minimum(full + rf, rs, S));
+        if (!many) {
+            if (rf < rem) atomicMin(&mins[full + rf], minimum(full + rf, rs, S));
+        } else {
+            const uint32_t F = 64 / S;
+            for (uint32_t f0 = full; f0 < LK; f0 += F)
+                if (rf < F && f0 + rf < LK) atomicMin(&mins[f0 + rf], minimum(f0 + rf, rs, S));
+        }
     }
     lds_fence();
     for (uint32_t t = lane; t < L; t += 64) {
@@ -180,6 +225,22 @@ __global__ __launch_bounds__(256) void minhash_kernel(const ItemT *__restrict__ 
         for (uint32_t j = 0; j < K; ++j) h = splitmix_finalize(h ^ (uint64_t)mins[t * K + j]);
         codes[set * L + t] = (uint32_t)(h >> (64 - bbits));
     }
+}
+
+// Slices of the items for r < 64 functions where several passes over a part of
+// them take fewer rounds of evaluations than one pass (0 where not), for a set of
+// 64 items, each pass costing about four rounds more: 40 functions in one pass
+// leave 24 lanes idle, two passes of 21 in three slices one (20,000 sets of 81
+// 64-bit items 69 -> 54 us).
+uint32_t choose_slices(uint32_t r) {
+    auto cost = [&](uint32_t S) { return (r + 64 / S - 1) / (64 / S) * ((64 + S - 1) / S + 4); };
+    uint32_t best = 0, least = r ? cost(64 / r) : 0;
+    for (uint32_t S = 1; r && S <= 64; ++S)
+        if (cost(S) < least) {
+            least = cost(S);
+            best = S;
+        }
+    return best;
 }
 
 template <typename ItemT, bool TEXT>
@@ -193,9 +254,14 @@ void launch_minhash(const ItemT *items, const uint64_t *offs, const TextSource &
     unsigned waves = 4;
     while (waves > 1 && waves * per_wave > 65536) waves >>= 1;
     dim3 grid((unsigned)((n + waves - 1) / waves)), block(64 * waves);
-    hipLaunchKernelGGL((minhash_kernel<ItemT, TEXT>), grid, block, waves * per_wave, s, items, offs, tx, n,
-                       K, L, b, key, codes);
-    FL_CHECK_LAUNCH();
+    const uint32_t slices = choose_slices(L * K & 63);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, waves * per_wave, s, items, offs, tx, n, K, L, b, key, slices,
+                           codes);
+        FL_CHECK_LAUNCH();
+    };
+    if (slices) go(minhash_kernel<ItemT, TEXT, true>);
+    else go(minhash_kernel<ItemT, TEXT, false>);
 }
 
 }  // namespace

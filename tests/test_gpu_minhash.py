@@ -59,3 +59,29 @@ def test_text_codes_at_the_splits(fl, family, gram, radix):
     want = oi.query((it, of), 7)
     got = ga.query_text((sym, offs), (gram, radix, key), 7)
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("family", [2, 3])
+@pytest.mark.parametrize("K,L", [(1, 1), (2, 4), (1, 9), (1, 12), (1, 21), (1, 22), (1, 23), (1, 32), (1, 33),
+                                 (1, 40), (1, 48), (5, 12), (8, 8), (5, 21), (8, 13)])
+def test_codes_where_sets_are_not_staged(fl, family, K, L):
+    """Function counts whose sets are read by the lanes themselves up to a size, or
+    whose functions are taken in several passes above one; sets around the sizes."""
+    rng = np.random.default_rng(K * 70 + L)
+    LK = K * L
+    near = [8, 12, 32, 16 * (64 // LK if LK < 64 else 1)]
+    sizes = np.array([0, 1, 2] + [s + d for s in near for d in (-1, 0, 1, 2)] + [130, 300])
+    offs = np.zeros(len(sizes) + 1, dtype=np.uint64)
+    offs[1:] = np.cumsum(sizes)
+    dt = np.uint64 if family == 3 else np.uint32
+    items = rng.integers(0, 2**64 if family == 3 else 2**32, int(offs[-1]), dtype=np.uint64).astype(dt)
+    log("minhash not staged", family, K, L)
+    gi = fl.Index((items, offs), family, K, L, 2, 5, seed=K + L, bucket_bits=19)
+    want = oracle.minhash_codes(items.astype(np.uint64), offs, K + L, K, L, 19)
+    assert np.array_equal(gi.debug_hash((items, offs)), want)
+    # the same as text: sets of one-symbol windows
+    sym = rng.integers(0, 256, int(offs[-1])).astype(np.uint8)
+    it, of = oracle.text_items(sym, offs, 1, 256, 77, 64 if family == 3 else 32)
+    got = gi.query_text((sym, offs), (1, 256, 77), 3)
+    want = gi.query((it, of), 3)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
