@@ -454,12 +454,14 @@ __device__ inline void walk_append(const uint16_t *lbs, const uint32_t *lps, uin
 }
 
 // GK: the general-k decode (k > 64) instead of the per-wavefront register
-// top-k.  PERS: the persistent grid, whose workgroups pull queries from a
-// device counter; otherwise one workgroup per query.  Each combination is
-// compiled separately so that the common path carries only its own code and
-// registers (the persistent loop keeps more values live).  WAVES: the
-// wavefronts per SIMD the register allocation must allow.
-template <typename CellT, int RP, int QT, bool GK, bool PERS, int WAVES>
+// top-k.  GRID: one workgroup per query; the persistent grid, whose workgroups
+// pull queries from a device counter; or one whose workgroups take the queries
+// that the sparse kernel deferred.  Each combination is compiled separately so
+// that the common path carries only its own code and registers (the loops keep
+// more values live).  WAVES: the wavefronts per SIMD the register allocation
+// must allow.
+enum { ONE_EACH, PULLED, DEFERRED_ONLY };
+template <typename CellT, int RP, int QT, bool GK, int GRID, int WAVES>
 __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     constexpr int QW = QT / 64;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -490,6 +492,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     const CellT *cells = static_cast<const CellT *>(A.cells);
 
     uint64_t q = blockIdx.x;
+    constexpr bool PERS = GRID != ONE_EACH;
     // the sparse kernel's deferred queries, 64 of the batch at a time: wavefront 0
     // reads the marks of a chunk and claims one query after another from them (an
     // exchange of the mark).  As many workgroups as the grid has for a chunk share
@@ -503,10 +506,10 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     const uint32_t nchunks = (uint32_t)((A.nq + 63) / 64);
     uint32_t dchunk = 0, dnext = 0, dempty = 2, dvisits = 0;
     unsigned long long dmask = 0;
-    if constexpr (PERS) dnext = blockIdx.x % nchunks;
+    if constexpr (GRID == DEFERRED_ONLY) dnext = blockIdx.x % nchunks;
     for (;;) {
         if constexpr (PERS) {
-            if (A.deferred) {
+            if constexpr (GRID == DEFERRED_ONLY) {
                 if (wave == 0) {
                     uint32_t got = ~0u;  // none left
                     for (;;) {
@@ -1264,11 +1267,11 @@ static int num_cus() {
     return v;
 }
 
-template <typename CellT, int RP, int QT, bool GK, bool PERS, int WAVES>
+template <typename CellT, int RP, int QT, bool GK, int GRID, int WAVES>
 static void launch_kernel(const QArgs &a, size_t lds, unsigned grid, hipStream_t s) {
     // once per kernel variant and process (a throwing initialiser is retried)
     static const bool attrs_ok = [] {
-        const void *fn = reinterpret_cast<const void *>(&query_kernel<CellT, RP, QT, GK, PERS, WAVES>);
+        const void *fn = reinterpret_cast<const void *>(&query_kernel<CellT, RP, QT, GK, GRID, WAVES>);
         (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds());
         // the counters are addressed from LDS address 0 (dynamic LDS first)
         hipFuncAttributes fa{};
@@ -1277,7 +1280,7 @@ static void launch_kernel(const QArgs &a, size_t lds, unsigned grid, hipStream_t
         return true;
     }();
     (void)attrs_ok;
-    hipLaunchKernelGGL((query_kernel<CellT, RP, QT, GK, PERS, WAVES>), dim3(grid), dim3(QT), lds, s, a);
+    hipLaunchKernelGGL((query_kernel<CellT, RP, QT, GK, GRID, WAVES>), dim3(grid), dim3(QT), lds, s, a);
 }
 
 template <typename CellT, int RP, int QT, bool GK>
@@ -1298,20 +1301,24 @@ static void launch_rp(const QArgs &a, size_t lds, bool persistent, hipStream_t s
     // many wavefronts per SIMD as the LDS lets share a CU (six to eight
     // four-wavefront workgroups); the others take what they need.
     if constexpr (QT == 256 && !GK) {
-        if (persistent)
-            launch_kernel<CellT, RP, QT, GK, true, 4>(a, lds, (unsigned)grid, s);
+        if (a.deferred)
+            launch_kernel<CellT, RP, QT, GK, DEFERRED_ONLY, 4>(a, lds, (unsigned)grid, s);
+        else if (persistent)
+            launch_kernel<CellT, RP, QT, GK, PULLED, 4>(a, lds, (unsigned)grid, s);
         else if (lds * 8 <= (size_t)max_lds())
-            launch_kernel<CellT, RP, QT, GK, false, 8>(a, lds, (unsigned)grid, s);
+            launch_kernel<CellT, RP, QT, GK, ONE_EACH, 8>(a, lds, (unsigned)grid, s);
         else if (lds * 7 <= (size_t)max_lds())
-            launch_kernel<CellT, RP, QT, GK, false, 7>(a, lds, (unsigned)grid, s);
+            launch_kernel<CellT, RP, QT, GK, ONE_EACH, 7>(a, lds, (unsigned)grid, s);
         else
-            launch_kernel<CellT, RP, QT, GK, false, 6>(a, lds, (unsigned)grid, s);
+            launch_kernel<CellT, RP, QT, GK, ONE_EACH, 6>(a, lds, (unsigned)grid, s);
     } else {
         constexpr int W = QT == 256 ? 4 : 1;
-        if (persistent)
-            launch_kernel<CellT, RP, QT, GK, true, W>(a, lds, (unsigned)grid, s);
+        if (a.deferred) {  // (the sparse kernel takes no general k)
+            if constexpr (!GK) launch_kernel<CellT, RP, QT, GK, DEFERRED_ONLY, W>(a, lds, (unsigned)grid, s);
+        } else if (persistent)
+            launch_kernel<CellT, RP, QT, GK, PULLED, W>(a, lds, (unsigned)grid, s);
         else
-            launch_kernel<CellT, RP, QT, GK, false, W>(a, lds, (unsigned)grid, s);
+            launch_kernel<CellT, RP, QT, GK, ONE_EACH, W>(a, lds, (unsigned)grid, s);
     }
     FL_CHECK_LAUNCH();
 }
