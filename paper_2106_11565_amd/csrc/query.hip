@@ -351,7 +351,7 @@ __device__ inline void walk_cells_filtered(const uint16_t *lbs, uint32_t nl,
 // member's filter word is read first and its id and row only if it survives
 // (walk_cells_filtered).  A round adds at most T*V keys, so the workgroup only
 // meets to look at the buffer when it could overflow (`room` counts down), and
-// only sorts and cuts it to k, tightening the threshold, when it would.
+// only sorts and cuts it to k, tightening the threshold, when even V = 1 would.
 struct AppendState {
     uint64_t thr;   // keys at or above it cannot be among the k smallest
     uint32_t room;  // keys that surely still fit (uniform)
@@ -363,20 +363,20 @@ __device__ inline void walk_append(const uint16_t *lbs, const uint32_t *lps, uin
                                    const uint32_t *__restrict__ memr, const uint16_t *__restrict__ cmgr,
                                    const uint32_t *__restrict__ cflr, uint32_t R, uint32_t Bp,
                                    uint32_t mstride, uint32_t level, bool keep, bool filt, uint32_t f1b,
-                                   uint32_t f2b, uint32_t V, uint32_t k, uint32_t cap, uint64_t *buf,
-                                   uint32_t *misc, AppendState &as) {
+                                   uint32_t f2b, uint32_t k, uint32_t cap, uint64_t *buf, uint32_t *misc,
+                                   AppendState &as) {
     constexpr int RW = (RP + 1) / 2;
     const int tid = threadIdx.x, lane = tid % 64;
     const uint32_t lim = 256u - level;
     uint32_t rb[RP];
 #pragma unroll
     for (int r = 0; r < RP; ++r) rb[r] = ((uint32_t)r < R ? (uint32_t)r : R - 1) * Bp;
-    for (uint32_t off = 0; off < total; off += T * V) {
-        if (as.room < T * V) {
+    for (uint32_t off = 0, V = 0; off < total; off += T * V) {
+        if (as.room < T) {
             __syncthreads();
             const uint32_t nb = misc[M_BUFN];
             __syncthreads();
-            if (nb > cap - T * V) {
+            if (nb > cap - T) {
                 for (uint32_t i = nb + tid; i < cap; i += T) buf[i] = ~0ull;
                 __syncthreads();
                 wg_bitonic<T>(buf, cap);
@@ -388,6 +388,7 @@ __device__ inline void walk_append(const uint16_t *lbs, const uint32_t *lps, uin
                 as.room = cap - nb;
             }
         }
+        V = as.room / T < 4 ? as.room / T : 4;
         as.room -= T * V;
         uint64_t slot[4];
         uint32_t fw[4];
@@ -491,8 +492,8 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
     const uint64_t rstride = (uint64_t)B * A.mstride;
     const CellT *cells = static_cast<const CellT *>(A.cells);
 
-    uint64_t q = blockIdx.x;
     constexpr bool PERS = GRID != ONE_EACH;
+    uint64_t q = blockIdx.x;
     // the sparse kernel's deferred queries, 64 of the batch at a time: wavefront 0
     // reads the marks of a chunk and claims one query after another from them (an
     // exchange of the mark).  As many workgroups as the grid has for a chunk share
@@ -1012,7 +1013,6 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
             const bool filt = !keep && R >= 2;
             const uint32_t *cflr = A.cfl + rep * rstride;
             const uint32_t f1b = ((rep + 1) % R) * Bp, f2b = ((rep + 2) % R) * Bp;
-            const uint32_t V = (cap - k) / QT < 4 ? (cap - k) / QT : 4;
             uint32_t pass_members = 0;
             auto walk = [&](uint32_t nl) {  // nl <= QT listed cells
                 uint32_t tot;
@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                 __syncthreads();
                 pass_members += tot;
                 walk_append<RP, QT>(lb, lp, nl, tot, memr, cmgr, cflr, R, Bp, A.mstride, level, keep,
-                                    filt, f1b, f2b, V, k, cap, buf, misc, as);
+                                    filt, f1b, f2b, k, cap, buf, misc, as);
             };
             const uint32_t nrep = hist[rep * (L + 1) + level];
             if (nrep <= CL) {
@@ -1176,8 +1176,10 @@ static uint32_t cap_for(uint32_t k, int T) {
 static int max_lds();
 
 // Batches up to these sizes take 1024-thread workgroups whatever their state's
-// size (fast decode, general k).
-constexpr uint64_t WIDE_FAST = 64, WIDE_GENERAL = 1024;
+// size: the fast decode, and general k where queries meet any number of list
+// entries, MANY_ENTRIES / 32 or more, and MANY_ENTRIES or more.
+constexpr uint64_t WIDE_FAST = 64, WIDE_GENERAL[] = {256, 512, 1024};
+constexpr double MANY_ENTRIES = 16384.0;
 
 // Launch shape of the query kernel for one index, k and batch size.
 struct QShape {
@@ -1202,10 +1204,19 @@ static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool spar
     const size_t big = q_layout(L, R, Bp, cap_for(k, 1024), 1024, 1, gk).total;
     // small batches of queries with some work in them: 256-thread workgroups
     // would leave the chip part empty and the slowest query decides, so each
-    // gets 1024 threads (517 queries, k = 100, 21,000 entries each: 743 -> 300
-    // us; 30 queries, k = 10, thousands of entries: 119 -> 36 us a call; one of
-    // 74 entries stays at 16 us with 256 threads and would take 20)
-    const bool wide = nq <= (gk ? WIDE_GENERAL : WIDE_FAST) && mean_entries >= 512.0 && big <= lim;
+    // gets 1024 threads (30 queries, k = 10, thousands of entries: 119 -> 36 us a
+    // call; one of 74 entries stays at 16 us with 256 threads and would take 20).
+    // General k: a workgroup per compute unit, one round of them, is faster for
+    // every index (250 queries, k = 100: 2 x 16 x 4,096 cells 29 us against 35,
+    // 3 x 300 cells of 2,160 entries 104 against 198); two rounds are even or
+    // faster from 512 entries on (500 queries: 92 against 97 and 171 against
+    // 196) but not below (60 against 43); four are slower (1,000 queries: 167
+    // against 104), but for queries so long that the slowest decides (517 of
+    // 21,000 entries: 367 against 792)
+    const bool many = mean_entries >= MANY_ENTRIES;
+    const bool wide = big <= lim &&
+                      (gk ? nq <= WIDE_GENERAL[many ? 2 : mean_entries >= MANY_ENTRIES / 32 ? 1 : 0]
+                          : nq <= WIDE_FAST && mean_entries >= 512.0);
     if (small * 4 <= lim && !wide) {
         // a state this small holds few cells, so few counts collide: four
         // copies (more only add clearing and merging), none for sparse
@@ -1218,16 +1229,23 @@ static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool spar
     }
     while (sh.hc & (sh.hc - 1)) sh.hc &= sh.hc - 1;  // round down to a power of two
     sh.cap = cap_for(k, sh.T);
-    // general k: up to four appends per thread and round where the workgroup's
-    // share of the LDS has the room; two where queries meet few entries (many of
-    // them then end in a pass that keeps every member, and a larger buffer
-    // tightens its threshold later and takes longer to sort: 5,000 reads, k =
-    // 100, 176 us against 227)
+    // general k: room behind the k best for two appends of each thread before
+    // the buffer is sorted, for one in 1024-thread workgroups unless queries meet
+    // very many entries: a larger buffer takes longer to sort and tightens its
+    // threshold later, a smaller one is sorted more often (k = 100, one / two /
+    // four: 5,000 queries, 3 x 300 cells, 653 / 591 / 665 us; 1,000 queries, 8 x
+    // 8,192 cells, 1024 threads, 212 / 252 / 310; 517 of 21,000 entries 470 / 368
+    // / 393).  Also four times k rather than two (k = 2,000, 250 queries in 1024
+    // threads: 98 us against 130), with 256 threads where that leaves room for
+    // seven workgroups (k = 500, 5,000 queries, 3 x 300 cells: 910 against 1,072;
+    // 4 x 4,096 cells, where it takes a third of them, 526 against 498)
     if (gk) {
         const size_t share = sh.T == 256 && small * 4 <= lim ? lim / 4 : lim;
-        while (sh.cap < k + (mean_entries < 512.0 ? 2u : 4u) * (uint32_t)sh.T &&
-               q_layout(L, R, Bp, sh.cap * 2, sh.T, 1, gk).total <= share)
-            sh.cap *= 2;
+        auto grow = [&](uint32_t want, size_t room) {
+            while (sh.cap < want && q_layout(L, R, Bp, sh.cap * 2, sh.T, 1, gk).total <= room) sh.cap *= 2;
+        };
+        grow(k + (sh.T == 256 ? 512u : many ? 2048u : 1024u), share);
+        grow(4 * k, sh.T == 256 ? std::min(share, lim / 7) : share);
         while (sh.hc > 1 && q_layout(L, R, Bp, sh.cap, sh.T, sh.hc, gk).total > share) sh.hc >>= 1;
     }
     sh.lds = q_layout(L, R, Bp, sh.cap, sh.T, sh.hc, gk).total;

@@ -58,6 +58,22 @@ def test_batch_sizes_around_the_workgroup_rule(fl, nq, k, K):
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), pers
 
 
+@pytest.mark.parametrize("R,K,L,nq", [
+    (3, 14, 10, 256), (3, 14, 10, 257),  # any number of list entries
+    (3, 4, 10, 512), (3, 4, 10, 513),    # some 1,900 per query
+    (8, 2, 64, 1024), (8, 2, 64, 1025),  # all 32,768
+])
+@pytest.mark.parametrize("k", [65, 700])  # buffers of the smallest and of a larger size
+def test_general_k_around_the_workgroup_rule(fl, R, K, L, nq, k):
+    X, Q, _ = synth.dense_gmm(N=8000, d=16, n_centres=30, sigma=0.2, nq=nq)
+    gi = fl.Index(X, 0, K, L, R, 64, seed=81)
+    oi = oracle.OracleIndex(oracle.SRP_F32, X, K, L, R, 64, 81)
+    want = oi.query(Q, k)
+    log("general k, batch size", nq, "k", k, "R", R, "K", K, "L", L)
+    got = gi.query(Q, k)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
 def _sets(vals):
     return np.asarray(vals, dtype=np.uint32), np.arange(len(vals) + 1, dtype=np.uint64)
 
