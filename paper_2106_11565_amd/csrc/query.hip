@@ -1205,7 +1205,8 @@ static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool spar
     // small batches of queries with some work in them: 256-thread workgroups
     // would leave the chip part empty and the slowest query decides, so each
     // gets 1024 threads (30 queries, k = 10, thousands of entries: 119 -> 36 us a
-    // call; one of 74 entries stays at 16 us with 256 threads and would take 20).
+    // call; one of 74 entries stays at 16 us with 256 threads and would take 20;
+    // k = 64, whose sixteen lists take longer to merge than four, 61 us against 114).
     // General k: a workgroup per compute unit, one round of them, is faster for
     // every index (250 queries, k = 100: 2 x 16 x 4,096 cells 29 us against 35,
     // 3 x 300 cells of 2,160 entries 104 against 198); two rounds are even or
@@ -1216,7 +1217,7 @@ static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool spar
     const bool many = mean_entries >= MANY_ENTRIES;
     const bool wide = big <= lim &&
                       (gk ? nq <= WIDE_GENERAL[many ? 2 : mean_entries >= MANY_ENTRIES / 32 ? 1 : 0]
-                          : nq <= WIDE_FAST && mean_entries >= 512.0);
+                          : nq <= WIDE_FAST && k <= 32 && mean_entries >= 512.0);
     if (small * 4 <= lim && !wide) {
         // a state this small holds few cells, so few counts collide: four
         // copies (more only add clearing and merging), none for sparse
