@@ -210,8 +210,21 @@ __global__ __launch_bounds__(T) void threshold_kernel(TArgs A) {
     uint32_t rep = 0;
     for (uint32_t r = 1; r < R; ++r)
         if (npos[r] < npos[rep]) rep = r;
+    // a member's groups beyond the enumerated repetition and the two of its filter
+    // word (where the members' rows are read by the dozen, each group of one costs a
+    // load over 16 cache lines: reading all R, 12,000 queries with every cell of 4 x
+    // 100 positive took 1,742 us, the one that is left #)
+    auto others_positive = [&](const uint16_t *row) {
+        bool ok = true;
+        for (uint32_t i = 3, r = (rep + 3) % R; i < R; ++i, r = r + 1 < R ? r + 1 : 0)
+            ok &= count_of(cnt32, r * Bp + row[r]) >= t;
+        return ok;
+    };
+    // (with one repetition every member of a positive cell is reported: only if
+    // they fit the answer's list, or all would be walked twice; 12,000 queries, 5
+    // cells of 100, 163 us, # in order alone)
     if (t >= 1 && npos[rep] <= T_LIST && (npos[rep] <= FEW || npos[rep] * FEW <= B) &&
-        A.small_slots) {
+        A.small_slots && (R > 1 || npos[rep] * (uint64_t)A.mstride <= T_LIST)) {
         const uint32_t np = misc[T_NP];
         if (!longl && np <= T_LIST) {
             for (uint32_t i = tid; i < np; i += T) {
@@ -266,7 +279,7 @@ __global__ __launch_bounds__(T) void threshold_kernel(TArgs A) {
                     sl += m & 3u;
                     const uint16_t *row = cmgr + (uint64_t)sl * A.Rp;
                     bool in = memr[sl] != 0xFFFFFFFFu;  // not the cell's padding
-                    for (uint32_t r = 0; r < R; ++r) in &= count_of(cnt32, r * Bp + row[r]) >= t;
+                    in &= others_positive(row);
                     if (in) {
                         const uint32_t at = atomicAdd(&misc[T_TOTAL], 1u);
                         if (at < T_LIST) plist[at] = sl;  // the cells are in lb by now
@@ -321,10 +334,7 @@ __global__ __launch_bounds__(T) void threshold_kernel(TArgs A) {
                         bool ok = x[e] != 0xFFFFFFFFu &&  // not the cell's padding
                                   (R < 2 || (count_of(cnt32, f1b + (fw[e] & 0xFFFFu)) >= t &&
                                              count_of(cnt32, f2b + (fw[e] >> 16)) >= t));
-                        if (ok && R > 3) {
-                            const uint16_t *row = cmgr + (slot + e) * A.Rp;
-                            for (uint32_t r = 0; r < R; ++r) ok &= count_of(cnt32, r * Bp + row[r]) >= t;
-                        }
+                        if (ok && R > 3) ok = others_positive(cmgr + (slot + e) * A.Rp);
                         in |= ok ? 1u << e : 0u;
                     }
                 }

@@ -56,3 +56,13 @@ def test_threshold_equals_oracle_in_order(fl, N, R, B, K, L):
                 assert np.array_equal(ids[i][:n], w[:n]), (t, i)
                 assert np.all(ids[i][n:] == 0xFFFFFFFF), (t, i)
     log("positive cells", sorted(npos)[:6], "to", max(npos))
+
+
+@pytest.mark.parametrize("N,R,B,K,L", [
+    (900, 1, 4, 8, 8), (1000, 1, 4, 8, 8), (1100, 1, 4, 8, 8),  # one cell about fills the answer's list
+    (8000, 1, 400, 8, 8),      # few cells, whose members pass it together
+    (5000, 4, 100, 3, 8),      # every cell positive: one group left behind the filter
+    (3000, 16, 24, 4, 10),     # thirteen left
+])
+def test_threshold_where_members_pass_by_the_dozen(fl, N, R, B, K, L):
+    test_threshold_equals_oracle_in_order(fl, N, R, B, K, L)
