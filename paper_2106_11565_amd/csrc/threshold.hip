@@ -213,7 +213,7 @@ __global__ __launch_bounds__(T) void threshold_kernel(TArgs A) {
     // a member's groups beyond the enumerated repetition and the two of its filter
     // word (where the members' rows are read by the dozen, each group of one costs a
     // load over 16 cache lines: reading all R, 12,000 queries with every cell of 4 x
-    // 100 positive took 1,742 us, the one that is left #)
+    // 100 positive took 1,742 us, the one that is left 519)
     auto others_positive = [&](const uint16_t *row) {
         bool ok = true;
         for (uint32_t i = 3, r = (rep + 3) % R; i < R; ++i, r = r + 1 < R ? r + 1 : 0)
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(T) void threshold_kernel(TArgs A) {
     };
     // (with one repetition every member of a positive cell is reported: only if
     // they fit the answer's list, or all would be walked twice; 12,000 queries, 5
-    // cells of 100, 163 us, # in order alone)
+    // cells of 100, 164 us, 107 in order alone)
     if (t >= 1 && npos[rep] <= T_LIST && (npos[rep] <= FEW || npos[rep] * FEW <= B) &&
         A.small_slots && (R > 1 || npos[rep] * (uint64_t)A.mstride <= T_LIST)) {
         const uint32_t np = misc[T_NP];
