@@ -486,7 +486,10 @@ void launch_te(QArgs &a, uint32_t cell_bytes, hipStream_t s) {
 //   - general k (k > 64), or L beyond the workgroup;
 //   - grids whose general kernel has 256 threads (its counters are small) and
 //     queries that touch a good part of them: 4,096 cells at 8,901 entries
-//     take 92 us in the general kernel and were twice that here;
+//     take 92 us in the general kernel and were twice that here; nor where they
+//     touch more than an eighth of them (10,000 queries, k = 10, 192 entries in
+//     400 cells 146 us general, 161 here; 5,000, 180 in 900 cells, 65 and 77;
+//     180 in 2,000 cells 66 and 52);
 //   - batches that the general kernel takes in one or two rounds of workgroups
 //     (eight on a compute unit of 256 threads, one of 1024): the slowest query
 //     is then most of what there is to wait for, and the second launch (5-6 us to
@@ -498,6 +501,7 @@ int sparse_variant(const Index &ix, const QArgs &a) {
     if (a.nq < (a.threads == 1024 ? 384 : 4096)) return 0;
     const double m = ix.mean_entries;
     auto fits = [&](int threads) { return a.nq * threads < (1ull << 32); };
+    if (a.threads != 1024 && m * 8 > (double)a.R * a.B) return 0;
     if (m <= 0.4 * 1024 && a.L <= 128) return fits(128) ? 1 : 0;
     if (a.threads != 1024) return 0;
     if (m <= 0.4 * 4096) return fits(256) ? 2 : 0;

@@ -92,6 +92,14 @@ def test_every_variant_equals_oracle(fl, T, R, B, L, copies, heavy):
             oi.insert(_sets(vals[n0:]))
 
 
+@pytest.mark.parametrize("T,R,B,L,copies,heavy", [
+    (128, 2, 601, 70, 1, 30),   # L > 64; nearly an eighth of the cells touched
+    (128, 16, 97, 8, 1, 30),    # three words and a bit per repetition
+])
+def test_every_variant_of_small_grids_equals_oracle(fl, T, R, B, L, copies, heavy):
+    test_every_variant_equals_oracle(fl, T, R, B, L, copies, heavy)
+
+
 @pytest.mark.parametrize("R,B,L", [(4, 1000, 8), (8, 5000, 20)])
 @pytest.mark.parametrize("nq", [4097, 66001])  # one, and several chunks of 64 per workgroup
 @pytest.mark.parametrize("every", [1, 7, 64, 1001])
