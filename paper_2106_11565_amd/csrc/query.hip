@@ -851,8 +851,6 @@ __global__ __launch_bounds__(QT, WAVES) void query_kernel(QArgs A) {
                 misc[M_BUFN] = 0;
                 misc[M_NGE] = 0;
                 misc[M_NALL] = 0;
-                misc[M_THRLO] = 0xFFFFFFFFu;
-                misc[M_THRHI] = 0xFFFFFFFFu;
                 misc[M_LCNT] = 0;
                 misc[M_MEMB] = 0;
                 misc[M_GATH] = 0;

@@ -45,8 +45,8 @@ struct QArgs {
 constexpr uint32_t DEFERRED = 0xFFFFFFFFu, CLAIMED = 0xFFFFFFFEu;
 
 // misc slots
-enum { M_Q = 0, M_BUFN, M_NGE, M_NALL, M_LEVEL, M_REP, M_KEEPALL, M_NEXT, M_THRLO,
-       M_THRHI, M_LCNT, M_MEMB, M_THI, M_ST_ALL, M_ST_FINAL, M_ST_PASSES, M_NT, M_GATH,
+enum { M_Q = 0, M_BUFN, M_NGE, M_NALL, M_LEVEL, M_REP, M_KEEPALL, M_NEXT, M_LCNT, M_MEMB,
+       M_THI, M_ST_ALL, M_ST_FINAL, M_ST_PASSES, M_NT, M_GATH,
        M_ST_GATH, M_SCAN0 };
 
 // c / d for c < 2^24 and d >= 1, from the float quotient (within one of the

@@ -343,24 +343,16 @@ __global__ __launch_bounds__(T, 8) void sparse_query_kernel(QArgs A, SLayout lay
 
         // ---- 6. the wavefronts' kept keys, packed
         uint64_t *wlist = buf + k;
-        if constexpr (QW == 1) {
-            if (lane == 0) {  // one sorted list: nothing to merge (M_BUFN stays 0)
-                misc[M_NGE] = ws.n_ge;
-                misc[M_NALL] = ws.n_all;
-                misc[M_GATH] = ws.gathered;
-            }
-        } else {
-            const unsigned long long have = __ballot(ws.wl != ~0ull);  // lanes 0 .. n-1
-            uint32_t at = 0;
-            if (lane == 0) {
-                if (have) at = atomicAdd(&misc[M_BUFN], (uint32_t)__popcll(have));
-                if (ws.n_ge) atomicAdd(&misc[M_NGE], ws.n_ge);
-                if (ws.n_all) atomicAdd(&misc[M_NALL], ws.n_all);
-                if (A.stats) atomicAdd(&misc[M_GATH], ws.gathered);
-            }
-            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-            if (ws.wl != ~0ull) wlist[at + lane] = ws.wl;
+        const unsigned long long have = __ballot(ws.wl != ~0ull);  // lanes 0 .. n-1
+        uint32_t at = 0;
+        if (lane == 0) {
+            if (have) at = atomicAdd(&misc[M_BUFN], (uint32_t)__popcll(have));
+            if (ws.n_ge) atomicAdd(&misc[M_NGE], ws.n_ge);
+            if (ws.n_all) atomicAdd(&misc[M_NALL], ws.n_all);
+            if (A.stats) atomicAdd(&misc[M_GATH], ws.gathered);
         }
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        if (ws.wl != ~0ull) wlist[at + lane] = ws.wl;
         __syncthreads();
         const uint32_t nge = misc[M_NGE], nall = misc[M_NALL], nk = misc[M_BUFN];
         if (tid == 0) {
@@ -371,8 +363,7 @@ __global__ __launch_bounds__(T, 8) void sparse_query_kernel(QArgs A, SLayout lay
             const uint32_t nres = nall < k ? nall : k;
             if (nk <= 64) {
                 if (wave != 0) return;
-                const uint64_t v =
-                    QW == 1 ? ws.wl : wave_sort64((uint32_t)lane < nk ? wlist[lane] : ~0ull, lane);
+                const uint64_t v = wave_sort64((uint32_t)lane < nk ? wlist[lane] : ~0ull, lane);
                 if ((uint32_t)lane < nres) {
                     oid[lane] = (uint32_t)v;
                     if (osc) osc[lane] = 255u - (uint32_t)(v >> 56);

@@ -48,8 +48,8 @@ struct BatchPlan {
     size_t codes = 0, out = 0, work = 0, hash = 0, total = 0;
 };
 
-// nitems: set items, or symbols of text requests (one byte each; their
-// n-gram items are extracted into the hash scratch).
+// nitems: set items, or symbols of text requests (one byte each; the hash
+// kernel reads the n-gram items from them).
 static BatchPlan plan_batch(const Index &ix, uint64_t nq, uint64_t nitems, uint32_t k,
                             bool text = false) {
     BatchPlan b;
@@ -160,7 +160,7 @@ struct Request {
     uint64_t dev_values = 0;             // device-resident payload (borrowed)
     bool text = false;                   // symbol sequences (payload: symbols)
     uint32_t gram = 0, radix = 0;
-    uint64_t tkey = 0, nwin = 0;         // item key; n-gram windows
+    uint64_t tkey = 0;                   // item key
     uint32_t *out_ids = nullptr;         // device outputs (borrowed), or null:
     uint32_t *out_scores = nullptr;      // results are kept for wait()
     int pcls = -1;
@@ -740,10 +740,6 @@ static void submit_text_request(Server &S, uint32_t idx_slot, const flinng_text 
         if (i && r->offsets[i] < r->offsets[i - 1])
             fail(FLINNG_EINVAL, "text offsets must be nondecreasing");
         r->offsets[i] -= first;
-        if (i) {
-            const uint64_t len = r->offsets[i] - r->offsets[i - 1];
-            r->nwin += len >= q->gram ? len - q->gram + 1 : 0;
-        }
     }
     r->nitems = last - first;
     if (r->nitems && !q->symbols) fail(FLINNG_EINVAL, "text.symbols is NULL");
