@@ -151,6 +151,8 @@ int flinng_build(const flinng_params *p, const flinng_input *data,
  *           May be NULL.
  *  persistent  0: one workgroup per query; 1: a persistent grid that pulls
  *           queries from a device counter (for uneven batches in one launch).
+ *           Batches whose queries meet few list entries take a workgroup per
+ *           query either way, and a second launch for the uneven ones.
  * Device outputs: the call returns once the work is enqueued on `stream`.
  * Host outputs: the call synchronizes `stream`.  Queries only read the index,
  * so concurrent calls (from any threads, on any streams) are allowed, also
