@@ -169,21 +169,20 @@ class Workload:
         return (it[int(o[0]):int(o[-1])], (o - o[0]).astype(np.uint64))
 
     def build_roofline(self):
-        """Build inserts: N*L*R (bucket, cell) tuples, each read and written
-        once per 8-bit radix pass of its sort (8-byte keys)."""
-        R, L, N = self.R, self.L, self.cfg["N"]
-        cb = 1
-        while (1 << cb) < R * ((self.B + 3) & ~3):
-            cb += 1
-        bits = (self.K if self.dense else self.b) + cb
+        """Build: each table's points sorted by bucket code (N*L pairs of 8
+        bytes, read and written once per 8-bit radix pass), then the list
+        entries and the 2^bits offsets per table written."""
+        L, N = self.L, self.cfg["N"]
+        bits = self.K if self.dense else self.b
         passes = (bits + 7) // 8
-        tuples = N * L * R
-        byts = tuples * passes * 16
+        pairs = N * L
+        info = self.index.info
+        byts = pairs * passes * 16 + info.list_entries * info.cell_id_bytes + (L << bits) * 4
         gbs = byts / self.build_s / 1e9
-        return {"kernel": "index build (hash, groups, per-table radix sort, dedup, CSR)",
-                "workload": self.name, "bound": "hbm", "tuples": tuples, "sort_passes": passes,
-                "alg_bytes": byts, "build_s": round(self.build_s, 4),
-                "tuples_per_s": round(tuples / self.build_s, 1),
+        return {"kernel": "index build (hash, groups, points sorted per table, lists, members)",
+                "workload": self.name, "bound": "hbm", "pairs": pairs, "sort_passes": passes,
+                "list_entries": info.list_entries, "alg_bytes": byts, "build_s": round(self.build_s, 4),
+                "pairs_per_s": round(pairs / self.build_s, 1),
                 "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(gbs / HBM_PEAK_GBS, 4)}
 
@@ -251,36 +250,36 @@ def stages(w, torch, fl, steps, persistent, out):
     decode_once(stats)
     torch.cuda.synchronize()
     st = [int(v) for v in stats.cpu().tolist()]
-    # algorithmic bytes of one decode launch: codes (L*4) and bucket offset
-    # pairs (L*8) per query, every list entry read, and for each member of
-    # the final pass's cells its id and its R group ids (4 + 2R B: the
-    # decode minimum of the straightforward walk), and k ids + scores out.
-    # The kernel itself reads less: a 4-byte filter word per member and the
-    # id and row only of the members that pass it (touched_bytes).
+    # bytes that the decode kernels ask for: codes (L*4) and bucket offset
+    # pairs (L*8) per query, every list entry, a 4-byte filter word per member
+    # of the final pass's cells, the id and row (4 + 2 Rp bytes) of the members
+    # that pass the filter, and k ids + scores out.  walk_bytes: what reading
+    # each of those members' id and R group ids would take instead (4 + 2R).
     cb = w.index.info.cell_id_bytes
     Rp = 1
     while Rp < w.R:
         Rp *= 2
-    alg = w.nq * w.L * 12 + st[0] * cb + st[2] * (4 + 2 * w.R) + w.nq * w.k * 8
-    touched = w.nq * w.L * 12 + st[0] * cb + st[2] * 4 + st[4] * (4 + 2 * Rp) + w.nq * w.k * 8
+    walk = w.nq * w.L * 12 + st[0] * cb + st[2] * (4 + 2 * w.R) + w.nq * w.k * 8
+    alg = w.nq * w.L * 12 + st[0] * cb + st[2] * 4 + st[4] * (4 + 2 * Rp) + w.nq * w.k * 8
     ach = alg / (decode_ms / 1e3) / 1e9
-    roof = {"kernel": "query_kernel (count + threshold + decode)", "workload": w.name,
+    roof = {"kernel": "sparse_query_kernel + query_kernel (count + threshold + decode)",
+            "workload": w.name,
             "K": w.K, "L": w.L, "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": measured_traffic(w),
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-scaled; "
                             "read from the committed counter summary for this kernel source)",
             "alg_bytes_per_launch": int(alg), "launch_ms": round(decode_ms, 4),
             "list_entries": st[0], "members_all_passes": st[1], "members_final": st[2],
-            "passes": st[3], "rows_gathered_final": st[4], "touched_bytes_per_launch": int(touched)}
+            "passes": st[3], "rows_gathered_final": st[4], "walk_bytes_per_launch": int(walk)}
     out = {"hash_ms": hash_ms, "decode_ms": decode_ms, "query_roofline": roof}
     if w.dense:
-        # the hash stage (one srp_fused_kernel launch: norms, bf16 MFMA
-        # projection, FP64 recheck, pack) against the dense bf16 matrix-core
-        # peak
+        # the hash stage (bf16 rows: one srp_fused_kernel launch with norms,
+        # MFMA projection, FP64 recheck and pack; fp32 rows: prep, projection
+        # and recheck kernels) against the dense bf16 matrix-core peak
         flops = 2.0 * w.nq * w.cfg["d"] * w.K * w.L
         tf = flops / (hash_ms / 1e3) / 1e12
         out["hash_roofline"] = {
-            "kernel": "SRP hash stage (srp_fused_kernel: projection + certificate + recheck + pack)",
+            "kernel": "SRP hash stage (projection + certificate + recheck + pack)",
             "workload": w.name, "K": w.K, "L": w.L, "bound": "mfma", "achieved": round(tf, 2),
             "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tf / BF16_PEAK_TFLOPS, 4),
             "alg_flops_per_launch": flops, "launch_ms": round(hash_ms, 4), "traffic": None}
@@ -290,16 +289,19 @@ def stages(w, torch, fl, steps, persistent, out):
 
 
 def measured_traffic(w):
-    """HBM bytes per query_kernel launch from the committed counter summary
-    (two rocprofv3 --pmc passes, scaled by a plain copy of known size), if
-    it was taken for this workload and (K, L) with the current kernel
-    source; None otherwise."""
+    """HBM bytes per decode launch (both query kernels) from the committed
+    counter summary (two rocprofv3 --pmc passes, scaled by a plain copy of
+    known size), if it was taken for this workload and (K, L) with the
+    current kernel sources; None otherwise."""
     import hashlib
-    src = os.path.join(ROOT, "paper_2106_11565_amd", "csrc", "query.hip")
     path = os.path.join(ROOT, "profiles", "traffic_query_kernel.md")
     if not os.path.exists(path):
         return None
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ("query.hip", "query_sparse.hip", "query_common.h"):
+        with open(os.path.join(ROOT, "paper_2106_11565_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    sha = h.hexdigest()[:16]
     for line in open(path):
         cols = [c.strip() for c in line.strip().strip("|").split("|")]
         if len(cols) >= 9 and cols[0] == w.cfg["name"] and cols[1] == str(w.K) and cols[2] == str(w.L):

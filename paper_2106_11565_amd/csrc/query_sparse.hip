@@ -29,9 +29,13 @@
 //   6. the wavefronts' nonempty top-k entries are packed together: at most 64
 //      in nearly every query, sorted and written out by one wavefront.
 //
-// What bounds it: vector instructions (the SIMDs are 55-85% busy), not memory:
-// 10,000 ReLU queries move 1.04 GB in 368 us (2.8 TB/s; 803 us in the general
-// kernel), URL queries 1.2 GB in 411 us.
+// What bounds it: vector instructions and the chain of dependent reads; for
+// 10,000 ReLU queries the vector units are busy 72% of 357 us (803 us in the
+// general kernel), the LDS 38%.  Held to 64 registers for eight wavefronts per
+// SIMD, it spills 20, 56 and 144 bytes per lane at Rp = 4, 8 and 16 (none at 1
+// and 2): of the 1.45 GB that those queries move (4 TB/s), 0.26 GB are such
+// stores and 0.66 GB what the kernel asks for.  10,000 URL queries, 8 x 16,384
+// cells: 416 us (general 1,138) and 1.5 GB.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
