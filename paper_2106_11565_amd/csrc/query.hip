@@ -1206,8 +1206,8 @@ static QShape q_shape(uint32_t L, uint32_t R, uint32_t Bp, uint32_t k, bool spar
     // call; one of 74 entries stays at 16 us with 256 threads and would take 20;
     // k = 64, whose sixteen lists take longer to merge than four, 61 us against 114).
     // General k: a workgroup per compute unit, one round of them, is faster for
-    // every index (250 queries, k = 100: 2 x 16 x 4,096 cells 29 us against 35,
-    // 3 x 300 cells of 2,160 entries 104 against 198); two rounds are even or
+    // every index (250 queries, k = 100: 96 entries in 4 x 4,096 cells 29 us
+    // against 35, 2,160 in 3 x 300 cells 104 against 198); two rounds are even or
     // faster from 512 entries on (500 queries: 92 against 97 and 171 against
     // 196) but not below (60 against 43); four are slower (1,000 queries: 167
     // against 104), but for queries so long that the slowest decides (517 of
